@@ -93,9 +93,6 @@ struct StageRef {
 static_assert(BM == BN && BM * 64 * 2 <= BM * ROWB,
               "the tile's rows of t and L2t (up to rank 64) must fit in one tile buffer of a stage");
 
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
 // waits for this wave's LDS reads, then a workgroup barrier (outstanding
 // global-to-LDS copies stay in flight)
 __device__ __forceinline__ void lds_wait_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -117,31 +114,6 @@ __device__ __forceinline__ float lds_load4_volatile(const float* p) {
 __device__ __forceinline__ uint32_t lds_load4_volatile(const uint32_t* p) {
   typedef const volatile __attribute__((address_space(3))) uint32_t lds_u;
   return *(lds_u*)(p);
-}
-
-// bf16 bits of (a, b) rounded to nearest even, a in the low half
-__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));
-}
-
-// The scale products sw * sx of two 32 x 32 blocks (lane l: sw of the weight
-// row l%32 (A side), sx of the token l%32 of B block l/32), in the result
-// layout of the integer blocks.  Each scale is split into two bf16 pieces,
-// hi = bf16(s) and lo = bf16(s - hi) (the difference is exact in float32), and
-// one v_mfma_f32_32x32x4_2b_bf16 sums the four exact products of
-// [hi, lo, hi, lo] (sw, the packed pieces hi | lo << 16 the weight pack wrote,
-// twice) and [hi, hi, lo, lo] (sx, split here) in float32.  That is the product
-// of the two 16-bit splits, each within 2^-16 of its scale, so the result is
-// within about 2^-15 of sw * sx.  Unlike the float32 outer-product MFMA, the
-// bf16 one lets the SIMD issue VALU work while it runs.
-__device__ __forceinline__ v32f scale_outer(uint32_t wpieces, float sx) {
-  typedef short v4s __attribute__((ext_vector_type(4)));
-  const uint32_t hx = bf16_pair(sx, sx);
-  const float lo_x = sx - __builtin_bit_cast(float, hx << 16);
-  const uint32_t lx = bf16_pair(lo_x, lo_x);
-  const v4s a = __builtin_bit_cast(v4s, static_cast<uint64_t>(wpieces) | (static_cast<uint64_t>(wpieces) << 32));
-  const v4s b = __builtin_bit_cast(v4s, static_cast<uint64_t>(hx) | (static_cast<uint64_t>(lx) << 32));
-  return __builtin_amdgcn_mfma_f32_32x32x4bf16_1k(a, b, v32f{}, 0, 0, 0);
 }
 
 // Tile of workgroup `bid`: XCD-major remap (hardware places workgroup b on XCD
@@ -674,6 +646,45 @@ static hipError_t launch_asp_gemm_gs(int M, int N, int K, int r, const uint8_t* 
   return hipGetLastError();
 }
 
+// The kernel for M > kSmallM tokens, by its estimated time.  A form whose
+// workgroups fit two to a CU runs in rounds of 512 tiles; a last round of at
+// most 256 leaves each CU one tile and is shorter.  Each round costs a start-up
+// and a part in proportion to K; the constants (in ns and ns per 1024
+// channels) are a least-squares fit, mean error 3-5%, of all forms timed at
+// 266 shapes (M = 65 .. 2048, K = 576 .. 14336, N = 1024 .. 9216, both group
+// sizes), where this rule's choice is on average 0.3% and at most 8% slower
+// than the fastest form.  Both sides at group 64, large tiles / choice:
+// M = 100, K = N = 3072 18.9 / 6.2 us; M = 415, K = 14336, N = 3072
+// 75.7 / 35.7 us; M = 512, K = 576, N = 3072 8.0 / 6.9 us; M = 333, K = 3072,
+// N = 9216 23.1 (kept) / 25.1 us; M = 4096 always the large tiles.
+struct FormCost {
+  int start, round, round_k, last, last_k;   // last, last_k: a last round of at most 256 tiles
+};
+
+static int64_t form_ns(const FormCost& c, int64_t tiles, int per_cu, int K) {
+  const auto time = [&](int a, int b) { return a + static_cast<int64_t>(b) * K / 1024; };
+  const int64_t slots = 256 * per_cu;
+  const int64_t full = tiles / slots, rest = tiles % slots;
+  int64_t ns = c.start + full * time(c.round, c.round_k);
+  if (rest > 0) ns += per_cu == 2 && rest <= 256 ? time(c.last, c.last_k) : time(c.round, c.round_k);
+  return ns;
+}
+
+static MidForm gemm_form(int M, int N, int K, int group) {
+  // large tiles; 32 x 64 by eight waves; 32 x 64 by four; 64 x 64 by four
+  static const FormCost cost[2][4] = {
+      {{2160, 5320, 8000, 2740, 5070}, {1930, 2370, 860, 0, 0}, {2660, 1960, 1500, 1240, 1030}, {2580, 2800, 2360, 1780, 1560}},
+      {{2670, 7230, 13090, 3170, 10500}, {1890, 2520, 1300, 0, 0}, {2980, 1910, 2280, 970, 1420}, {3030, 3210, 3960, 1850, 2750}}};
+  const FormCost* c = cost[group == 32 ? 1 : 0];
+  const auto tiles = [&](int tm, int tn) { return static_cast<int64_t>((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  const int64_t ns[4] = {form_ns(c[0], tiles(BM, BN), 2, K), form_ns(c[1], tiles(32, 64), 1, K),
+                         form_ns(c[2], tiles(32, 64), 2, K), form_ns(c[3], tiles(64, 64), 2, K)};
+  int best = 0;
+  for (int i = 1; i < 4; ++i)
+    if (ns[i] < (best == 0 ? ns[0] - ns[0] / 32 : ns[best])) best = i;   // within 3%: the large tiles
+  return static_cast<MidForm>(best);
+}
+
 // few tokens: the float32 scales (asp_gemm_small_kernel); otherwise the
 // weight-scale pieces
 hipError_t launch_asp_gemm(int M, int N, int K, int r, int group, const uint8_t* xq, const float* xs,
@@ -681,6 +692,9 @@ hipError_t launch_asp_gemm(int M, int N, int K, int r, int group, const uint8_t*
                            const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                            hipStream_t stream) {
   if (M <= kSmallM) return launch_asp_gemm_small(M, N, K, r, group, xq, xs, t, wq, ws, L2t, bias, y, stream);
+  const MidForm form = gemm_form(M, N, K, group);
+  if (form != MidForm::kNone)
+    return launch_asp_gemm_mid(form, M, N, K, r, group, xq, xs, t, wq, wsp, L2t, bias, y, stream);
   return group == 32 ? launch_asp_gemm_gs<32>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream)
                      : launch_asp_gemm_gs<64>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream);
 }

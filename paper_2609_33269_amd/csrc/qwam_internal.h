@@ -54,6 +54,13 @@ hipError_t launch_asp_gemm_small(int M, int N, int K, int r, int group, const ui
                                  const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                                  hipStream_t stream);
 
+// the GEMM in tiles of 32 or 64 tokens x 64 channels with K split over the
+// workgroup's waves, for a few hundred tokens
+enum class MidForm { kNone = 0, k32x64Waves8 = 1, k32x64Waves4 = 2, k64x64Waves4 = 3 };
+hipError_t launch_asp_gemm_mid(MidForm form, int M, int N, int K, int r, int group, const uint8_t* xq,
+                               const float* xs, const uint16_t* t, const uint8_t* wq, const uint32_t* wsp,
+                               const uint16_t* L2t, const uint16_t* bias, uint16_t* y, hipStream_t stream);
+
 // the whole layer for M <= kSmallM in one launch (r = 16 or 32, group 64, no
 // rotation); xq / xs / t are optional outputs (all null or none)
 hipError_t launch_asp_layer_small(int M, int N, int K, int r, const uint16_t* x, const float* inv_smooth,

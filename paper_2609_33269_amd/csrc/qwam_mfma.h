@@ -1,7 +1,8 @@
 // Matrix-core helpers shared by the ASP GEMM kernels (gfx950): the FP6 view
 // of packed code blocks, the exact integer partial of one group on
-// v_mfma_scale_f32_32x32x64_f8f6f4, and the per-group float32 scaling of a
-// 32 x 32 result block with the row scales broadcast by DPP.
+// v_mfma_scale_f32_32x32x64_f8f6f4, the per-group scale products on the bf16
+// matrix cores, and the float32 scaling of a 32 x 32 result block with the row
+// scales broadcast by DPP.
 #pragma once
 #include <utility>
 
@@ -37,6 +38,34 @@ constexpr int kE8M0Code = 127 + 3;
 // on both operands the products underflow to zero)
 __device__ __forceinline__ v16f fp6_partial(const v8i& a, const v8i& b, int sa, int sb) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, v16f{}, kFmtFp6, kFmtFp6, 0, sa, 0, sb);
+}
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+
+// bf16 bits of (a, b) rounded to nearest even, a in the low half
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));
+}
+
+// The scale products sw * sx of two 32 x 32 blocks (lane l: sw of the weight
+// row l%32 (A side), sx of the token l%32 of B block l/32), in the result
+// layout of the integer blocks.  Each scale is split into two bf16 pieces,
+// hi = bf16(s) and lo = bf16(s - hi) (the difference is exact in float32), and
+// one v_mfma_f32_32x32x4_2b_bf16 sums the four exact products of
+// [hi, lo, hi, lo] (sw, the packed pieces hi | lo << 16 the weight pack wrote,
+// twice) and [hi, hi, lo, lo] (sx, split here) in float32.  That is the product
+// of the two 16-bit splits, each within 2^-16 of its scale, so the result is
+// within about 2^-15 of sw * sx.  Unlike the float32 outer-product MFMA, the
+// bf16 one lets the SIMD issue VALU work while it runs.
+__device__ __forceinline__ v32f scale_outer(uint32_t wpieces, float sx) {
+  typedef short v4s __attribute__((ext_vector_type(4)));
+  const uint32_t hx = bf16_pair(sx, sx);
+  const float lo_x = sx - __builtin_bit_cast(float, hx << 16);
+  const uint32_t lx = bf16_pair(lo_x, lo_x);
+  const v4s a = __builtin_bit_cast(v4s, static_cast<uint64_t>(wpieces) | (static_cast<uint64_t>(wpieces) << 32));
+  const v4s b = __builtin_bit_cast(v4s, static_cast<uint64_t>(hx) | (static_cast<uint64_t>(lx) << 32));
+  return __builtin_amdgcn_mfma_f32_32x32x4bf16_1k(a, b, v32f{}, 0, 0, 0);
 }
 
 // x of lane 16 * (lane / 16) + V (lane V of this lane's row of 16, DPP

@@ -1,0 +1,56 @@
+"""GPU parity of the GEMM for a few hundred tokens (tiles of 32 or 64 tokens x
+64 channels with K split over the workgroup's waves), at the edges of its
+tiles, stages and wave ranges: token remainders of one and tile - 1, N not a
+multiple of the tile, fewer spans than waves, spans that fill no whole stage,
+every rank, both group sizes, with and without a bias.
+
+y against the float64 oracle: the relative Frobenius tolerance of
+parity_helpers.check_y, and every element within the bound of the GEMM's
+arithmetic (parity_helpers.check_y_elements)."""
+
+import pytest
+import torch
+
+from oracle import qwam_oracle as O
+from paper_2609_33269_amd import inputs as I
+from paper_2609_33269_amd import qwam as Q
+
+from parity_helpers import bits, check_y, check_y_elements, gpu_layer, log, oracle_factors, run_gpu, y_abs_terms
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    Q.lib()
+
+
+SHAPES = [
+    # M, K, N, r, group, bias: the form the launcher's estimate picks
+    (65, 64, 16, 16, 64, True),        # 32 x 64, four waves: one span, three waves idle, 16 of 64 columns
+    (95, 448, 208, 32, 64, False),     # four waves, seven spans (last range one span), 31 of 32 tokens
+    (97, 832, 1040, 48, 32, True),     # group 32, one token of the last tile
+    (66, 7168, 80, 64, 64, True),      # 32 x 64, eight waves: deep K, ragged columns
+    (127, 14336, 64, 16, 32, False),   # eight waves, group 32
+    (257, 2112, 2000, 32, 64, True),   # 64 x 64, four waves: one token of the last tile, 33 spans
+    (383, 1600, 2064, 64, 32, False),  # 64 x 64, group 32, rank 64, 25 spans
+]
+
+
+@pytest.mark.parametrize("M,K,N,r,group,bias", SHAPES)
+def test_mid_gemm_parity(M, K, N, r, group, bias):
+    d = I.custom(M, K, N, r, seed=17 + M, n_outliers=3, with_bias=bias)
+    f = dict(oracle_factors(d), group=group)
+    log(f"  mid GEMM M={M} K={K} N={N} r={r} group={group} bias={bias}")
+    ref = O.asp_linear(d.x, f, bias_bits=d.bias)
+    layer = gpu_layer(f, d.bias)
+    x, xq, xs, t, y = run_gpu(layer, d.x)
+    tg = bits(t)
+    y_t = ref["y"] + (O.bf16_bits_to_f64(tg) - O.bf16_bits_to_f64(ref["t"])) @ O.bf16_bits_to_f64(f["L2"])
+    at = y_abs_terms(ref["sx"], ref["sw"], ref["P"], tg, f["L2"], d.bias)
+    check_y_elements(bits(y), y_t, at, ref["P"].shape[2], r)
+    check_y(bits(y), ref["y"])
+    again = Q.asp_linear(layer, xq, xs, t)
+    assert torch.equal(again.view(torch.int16), y.view(torch.int16)), "the sum over the waves is in a fixed order"
