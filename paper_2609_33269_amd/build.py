@@ -1,4 +1,5 @@
-"""Build libqwam.so (HIP kernels for gfx950 + the C ABI) in-tree with hipcc.
+"""Build libqwam.so (HIP kernels for gfx950 + the C ABI) in-tree with hipcc, and
+the CPython module of its per-token calls (_qwam_call) with the host compiler.
 
 Usage: python -m paper_2609_33269_amd.build [-v]
 """
@@ -9,12 +10,14 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libqwam.so")
+CALL_MODULE = os.path.join(HERE, "_qwam_call.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -50,11 +53,33 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _build_call_module(verbose: bool) -> None:
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    tmp = CALL_MODULE + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           "-isystem", f"{tdir}/include", "-isystem", f"{tdir}/include/torch/csrc/api/include",
+           "-isystem", f"{rocm}/include", "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "qwam_binding.cpp"), "-o", tmp,
+           f"-L{tdir}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{tdir}/lib"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed on qwam_binding.cpp:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, CALL_MODULE)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libqwam.so; returns the library path."""
+    """Compile every source, link libqwam.so and the call module; returns the
+    library path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        call = ex.submit(_build_call_module, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        call.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

@@ -1,9 +1,14 @@
-"""Python binding of libqwam (ctypes): argument marshalling only.
+"""Python binding of libqwam: argument marshalling only.
 
 Every step of the layer runs in the library's HIP kernels; this module checks
 tensor devices, dtypes and shapes, allocates outputs with PyTorch and passes
 raw device pointers plus the current HIP stream across the C ABI.  If the
 library is not built, every call raises: there is no fallback.
+
+The per-token calls (quantize_act, quantize_act_deflated, asp_linear,
+asp_layer) marshal natively (csrc/qwam_binding.cpp); what that path does not
+take (an explicit stream, or an argument that fails a check) goes through
+ctypes here, which raises for the argument that is wrong.
 
 Names follow the C ABI (include/qwam.h): pack_weights, quantize_act,
 quantize_act_deflated, asp_linear, asp_layer, debug_group_partials,
@@ -14,6 +19,7 @@ probe_mfma, probe_valu_fma, probe_copy, probe_empty.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -87,6 +93,25 @@ def lib() -> ctypes.CDLL:
             f.argtypes = args
         _lib = handle
     return _lib
+
+
+_call = None
+
+
+def _native():
+    """The native module of the per-token calls, bound to the loaded library."""
+    global _call
+    if _call is None:
+        path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_qwam_call.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is not built; run `python -m paper_2609_33269_amd.build`")
+        spec = importlib.util.spec_from_file_location("_qwam_call", path)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.bind(*(ctypes.cast(getattr(lib(), f), ctypes.c_void_p).value
+                   for f in ("qwam_quantize_act", "qwam_quantize_act_deflated", "qwam_asp_linear", "qwam_asp_layer")))
+        _call = mod
+    return _call
 
 
 def _check(fn: str, status: int) -> None:
@@ -194,16 +219,22 @@ def quantize_act(layer: PackedLayer, x: torch.Tensor, stream=None, out=None):
     """qwam_quantize_act: x bf16 [M][K] -> (xq uint8 [M][K/2], xs float32 [K/64][M], t bf16 [M][r]).
 
     `out` may give the three output tensors (preallocated, e.g. for a benchmark loop)."""
-    return _quantize(lib().qwam_quantize_act, "qwam_quantize_act", layer, x, stream, out)
+    return _quantize(False, "qwam_quantize_act", layer, x, stream, out)
 
 
 def quantize_act_deflated(layer: PackedLayer, x: torch.Tensor, stream=None, out=None):
     """qwam_quantize_act_deflated: as quantize_act, but the codes are those of
     the deflated activation x~ - L1 t (Eq. 8 / Eq. 9)."""
-    return _quantize(lib().qwam_quantize_act_deflated, "qwam_quantize_act_deflated", layer, x, stream, out)
+    return _quantize(True, "qwam_quantize_act_deflated", layer, x, stream, out)
 
 
-def _quantize(fn, name: str, layer: PackedLayer, x: torch.Tensor, stream, out):
+def _quantize(deflated: bool, name: str, layer: PackedLayer, x: torch.Tensor, stream, out):
+    if stream is None:
+        done = (_call or _native()).quantize(layer, x, out, deflated)
+        if done is not None:
+            if type(done) is int:
+                _check(name, done)
+            return done
     M = x.shape[0]
     dev = x.device
     if out is None:
@@ -213,7 +244,8 @@ def _quantize(fn, name: str, layer: PackedLayer, x: torch.Tensor, stream, out):
     else:
         xq, xs, t = out
     c = layer.c_struct()
-    st = fn(ctypes.byref(c), M, _req(x, "x", torch.bfloat16, (M, layer.K)),
+    st = getattr(lib(), name)(
+            ctypes.byref(c), M, _req(x, "x", torch.bfloat16, (M, layer.K)),
             _req(xq, "xq", torch.uint8, (M, layer.K // 2)),
             _req(xs, "xs", torch.float32, (layer.K // layer.group, M)),
             _req(t, "t", torch.bfloat16, (M, layer.r)), _stream_ptr(stream))
@@ -224,6 +256,12 @@ def _quantize(fn, name: str, layer: PackedLayer, x: torch.Tensor, stream, out):
 def asp_linear(layer: PackedLayer, xq: torch.Tensor, xs: torch.Tensor, t: torch.Tensor,
                out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """qwam_asp_linear: -> y bf16 [M][N]."""
+    if stream is None:
+        y = (_call or _native()).linear(layer, xq, xs, t, out)
+        if y is not None:
+            if type(y) is int:
+                _check("qwam_asp_linear", y)
+            return y
     M = xq.shape[0]
     G = layer.K // layer.group
     y = torch.empty((M, layer.N), dtype=torch.bfloat16, device=xq.device) if out is None else out
@@ -247,6 +285,12 @@ def asp_layer(layer: PackedLayer, x: torch.Tensor, out=None, act_out=None, strea
     """qwam_asp_layer: the whole layer for M <= 64 tokens in one launch.
     x bf16 [M][K] -> y bf16 [M][N].  `act_out` = (xq, xs, t) receives the
     activation step's outputs as well (optional)."""
+    if stream is None and act_out is None:
+        y = (_call or _native()).layer(layer, x, out)
+        if y is not None:
+            if type(y) is int:
+                _check("qwam_asp_layer", y)
+            return y
     M = x.shape[0]
     y = torch.empty((M, layer.N), dtype=torch.bfloat16, device=x.device) if out is None else out
     c = layer.c_struct()
