@@ -206,6 +206,27 @@ qwam_status qwam_quantize_act_deflated(const qwam_layer *L, int32_t M, const uin
                                        uint8_t *xq, float *xs, uint16_t *t, void *stream);
 
 /*
+ * The two activation calls with an optional workspace.  With few tokens and a
+ * large K, one workgroup per 16 tokens leaves most of the chip idle; given a
+ * workspace, the call splits K over workgroups as well and adds the splits'
+ * partial sums of t in a fixed order (t then differs from the unsplit call's
+ * in float32 summation order only; deflated, in float64, so its bits agree).
+ *   deflated   0: as qwam_quantize_act; otherwise as qwam_quantize_act_deflated
+ *   workspace  device memory of at least qwam_quantize_act_workspace(L, M,
+ *              deflated) bytes, 16-byte aligned, owned by the caller; its
+ *              contents on entry do not matter; calls that share it must not
+ *              overlap.  NULL: as the calls without a workspace
+ */
+qwam_status qwam_quantize_act_ws(const qwam_layer *L, int32_t M, int32_t deflated, const uint16_t *x,
+                                 uint8_t *xq, float *xs, uint16_t *t, void *workspace,
+                                 int64_t workspace_bytes, void *stream);
+
+/* Bytes of workspace with which qwam_quantize_act_ws splits K for (L, M):
+ * 0 where it does not, -1 for an unsupported layer or M.  Reads K, r, group
+ * and hadamard of L only. */
+int64_t qwam_quantize_act_workspace(const qwam_layer *L, int32_t M, int32_t deflated);
+
+/*
  * The ASP GEMM (the second kernel of App. B.1): the integer partial sum of
  * every group, P[m, n, g] = sum_{k in g} qx[m, k] qw[n, k] (exact: the codes
  * are FP6 e2m3 operands of the matrix cores, every product and sum an integer

@@ -237,4 +237,38 @@ __device__ __forceinline__ void reduce_t(const T* red, int nwaves, int rows, uin
   }
 }
 
+// Token blocks whose K is split over workgroups (blockIdx.y): the workgroup's
+// sum over its waves goes to the workspace, part [split][16 gridDim.x][RANK].
+template <int RANK, typename T>
+__device__ __forceinline__ void store_split_t(const T* red, int nwaves, int m0, T* __restrict__ part) {
+  T* dst = part + (static_cast<int64_t>(blockIdx.y) * gridDim.x * 16 + m0) * RANK;
+  for (int e = threadIdx.x; e < 16 * RANK; e += blockDim.x) {
+    T sum = 0;
+    for (int w = 0; w < nwaves; ++w) sum += red[w * 16 * RANK + e];
+    dst[e] = sum;
+  }
+}
+
+// The second launch of a split deflated call: every workgroup of a token block
+// sums its double partials in split order and rounds once (the same bits in
+// each); -t as float into LDS, and t itself from the first split's workgroup.
+template <int RANK>
+__device__ __forceinline__ void combine_split_t(const double* __restrict__ part, int splits, int m0, int rows,
+                                                uint16_t* __restrict__ t_rows, float* tneg) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 16 * RANK;
+  const double* src = part + static_cast<int64_t>(m0) * RANK;
+  for (int e = threadIdx.x; e < 16 * RANK; e += blockDim.x) {
+    double sum = 0;
+#pragma unroll 8
+    for (int s = 0; s < splits; ++s) sum += src[s * stride + e];
+    const uint32_t b = f64_to_bf16_rne(sum);
+    if (blockIdx.y == 0 && e / RANK < rows) t_rows[e] = static_cast<uint16_t>(b);
+    tneg[e] = -bf16_to_f32(b);
+  }
+}
+
+// Which part of the deflated computation a launch does: all of it (K not
+// split), the partial sums of t, or the deflation and the codes.
+enum class Phase { kAll, kSums, kCodes };
+
 }  // namespace qwam

@@ -117,7 +117,8 @@ qwam_status qwam_pack_weights(int32_t K, int32_t N, int32_t group, const float* 
 namespace {
 
 qwam_status quantize_act_common(const char* fn, bool deflate, const qwam_layer* L, int32_t M,
-                                const uint16_t* x, uint8_t* xq, float* xs, uint16_t* t, void* stream) {
+                                const uint16_t* x, uint8_t* xq, float* xs, uint16_t* t, void* workspace,
+                                int64_t workspace_bytes, void* stream) {
   qwam_status s = check_layer(fn, L, true);
   if (s != QWAM_OK) return s;
   if ((s = check_m(fn, M)) != QWAM_OK) return s;
@@ -129,16 +130,24 @@ qwam_status quantize_act_common(const char* fn, bool deflate, const qwam_layer* 
   QWAM_REQUIRE_PTR(xq);
   QWAM_REQUIRE_PTR(xs);
   QWAM_REQUIRE_PTR(t);
+  if (workspace != nullptr) {
+    if (!aligned16(workspace)) return fail(QWAM_ERR_MISALIGNED, "%s: workspace is not 16-byte aligned", fn);
+    const int64_t need = qwam::act_workspace_bytes(M, L->K, L->r, L->hadamard, deflate);
+    if (workspace_bytes < need)
+      return fail(QWAM_ERR_INVALID_ARG, "%s: workspace of %lld bytes, %lld needed", fn,
+                  static_cast<long long>(workspace_bytes), static_cast<long long>(need));
+  }
   if ((s = check_device(fn)) != QWAM_OK) return s;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   if (L->hadamard != 0)
     return launched(fn, qwam::launch_quantize_act_rotated(M, L->K, L->r, L->group, L->hadamard, deflate, x,
                                                           L->inv_smooth, L->L1t, L->L1f, deflate ? L->L1 : nullptr,
-                                                          xq, xs, t, st));
+                                                          xq, xs, t, workspace, st));
   if (deflate)
     return launched(fn, qwam::launch_quantize_act_deflated(M, L->K, L->r, L->group, x, L->inv_smooth, L->L1f, L->L1,
-                                                           xq, xs, t, st));
-  return launched(fn, qwam::launch_quantize_act(M, L->K, L->r, L->group, x, L->inv_smooth, L->L1f, xq, xs, t, st));
+                                                           xq, xs, t, workspace, st));
+  return launched(fn, qwam::launch_quantize_act(M, L->K, L->r, L->group, x, L->inv_smooth, L->L1f, xq, xs, t, workspace,
+                                                st));
 }
 
 }  // namespace
@@ -147,12 +156,24 @@ extern "C" {
 
 qwam_status qwam_quantize_act(const qwam_layer* L, int32_t M, const uint16_t* x, uint8_t* xq, float* xs,
                               uint16_t* t, void* stream) {
-  return quantize_act_common("qwam_quantize_act", false, L, M, x, xq, xs, t, stream);
+  return quantize_act_common("qwam_quantize_act", false, L, M, x, xq, xs, t, nullptr, 0, stream);
 }
 
 qwam_status qwam_quantize_act_deflated(const qwam_layer* L, int32_t M, const uint16_t* x, uint8_t* xq,
                                        float* xs, uint16_t* t, void* stream) {
-  return quantize_act_common("qwam_quantize_act_deflated", true, L, M, x, xq, xs, t, stream);
+  return quantize_act_common("qwam_quantize_act_deflated", true, L, M, x, xq, xs, t, nullptr, 0, stream);
+}
+
+int64_t qwam_quantize_act_workspace(const qwam_layer* L, int32_t M, int32_t deflated) {
+  const char* fn = "qwam_quantize_act_workspace";
+  if (check_layer(fn, L, true) != QWAM_OK || check_m(fn, M) != QWAM_OK) return -1;
+  return qwam::act_workspace_bytes(M, L->K, L->r, L->hadamard, deflated != 0);
+}
+
+qwam_status qwam_quantize_act_ws(const qwam_layer* L, int32_t M, int32_t deflated, const uint16_t* x, uint8_t* xq,
+                                 float* xs, uint16_t* t, void* workspace, int64_t workspace_bytes, void* stream) {
+  return quantize_act_common(deflated != 0 ? "qwam_quantize_act_deflated" : "qwam_quantize_act", deflated != 0, L, M, x,
+                             xq, xs, t, workspace, workspace_bytes, stream);
 }
 
 qwam_status qwam_asp_linear(const qwam_layer* L, int32_t M, const uint8_t* xq, const float* xs,

@@ -28,7 +28,8 @@
 namespace {
 
 // entry points of the libqwam that qwam.py loaded
-decltype(&qwam_quantize_act) g_quantize[2];       // plain, deflated
+decltype(&qwam_quantize_act_ws) g_quantize;
+decltype(&qwam_quantize_act_workspace) g_workspace;
 decltype(&qwam_asp_linear) g_linear;
 decltype(&qwam_asp_layer) g_layer;
 
@@ -154,12 +155,19 @@ PyObject* py_quantize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
       !output(given[1], xt, at::kFloat, L.c.K / L.c.group, M, &xs.o, &ps) ||
       !output(given[2], xt, at::kBFloat16, M, L.c.r, &t.o, &pt))
     return none_or_error();
+  const int32_t deflated = PyObject_IsTrue(args[3]) == 1;
+  // few tokens and a large K: the call splits K over workgroups through a
+  // workspace, from the current stream's pool (dropped below: the next user of
+  // that memory runs behind the call's kernels)
+  const int64_t need = g_workspace(&L.c, static_cast<int32_t>(M), deflated);
+  at::Tensor ws;
+  if (need > 0) ws = at::empty({need}, xt.options().dtype(at::kByte));
+  void* const pw = need > 0 ? ws.data_ptr() : nullptr;
   void* stream = current_stream();
-  const auto fn = g_quantize[PyObject_IsTrue(args[3]) == 1];
   qwam_status st;
   Py_BEGIN_ALLOW_THREADS
-  st = fn(&L.c, static_cast<int32_t>(M), static_cast<const uint16_t*>(x), static_cast<uint8_t*>(pq),
-          static_cast<float*>(ps), static_cast<uint16_t*>(pt), stream);
+  st = g_quantize(&L.c, static_cast<int32_t>(M), deflated, static_cast<const uint16_t*>(x), static_cast<uint8_t*>(pq),
+                  static_cast<float*>(ps), static_cast<uint16_t*>(pt), pw, need > 0 ? need : 0, stream);
   Py_END_ALLOW_THREADS
   if (st != QWAM_OK) return PyLong_FromLong(st);
   return PyTuple_Pack(3, xq.o, xs.o, t.o);
@@ -210,12 +218,12 @@ PyObject* py_layer(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses of qwam_quantize_act, qwam_quantize_act_deflated, qwam_asp_linear, qwam_asp_layer)
+// bind(addresses of qwam_quantize_act_ws, qwam_quantize_act_workspace, qwam_asp_linear, qwam_asp_layer)
 PyObject* py_bind(PyObject*, PyObject* args) {
   unsigned long long a[4];
   if (!PyArg_ParseTuple(args, "KKKK", &a[0], &a[1], &a[2], &a[3])) return nullptr;
-  g_quantize[0] = reinterpret_cast<decltype(&qwam_quantize_act)>(a[0]);
-  g_quantize[1] = reinterpret_cast<decltype(&qwam_quantize_act)>(a[1]);
+  g_quantize = reinterpret_cast<decltype(&qwam_quantize_act_ws)>(a[0]);
+  g_workspace = reinterpret_cast<decltype(&qwam_quantize_act_workspace)>(a[1]);
   g_linear = reinterpret_cast<decltype(&qwam_asp_linear)>(a[2]);
   g_layer = reinterpret_cast<decltype(&qwam_asp_layer)>(a[3]);
   Py_RETURN_NONE;

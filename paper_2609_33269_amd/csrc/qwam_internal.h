@@ -11,21 +11,43 @@ hipError_t launch_pack_weights(int K, int N, int group, const float* R, const fl
 // L1f: the fragment-ordered copy of L1 (qwam_layer) that the activation
 // kernels' down-projection reads
 hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x, const float* inv_smooth,
-                               const uint16_t* L1f, uint8_t* xq, float* xs, uint16_t* t,
+                               const uint16_t* L1f, uint8_t* xq, float* xs, uint16_t* t, void* workspace,
                                hipStream_t stream);
 
 // the 4-bit path quantizes the deflated activation x~ - L1 t (Eq. 8 / Eq. 9);
 // L1 is [K][r] bf16 (the deflation's rows), L1t the same factor as [r][K]
 hipError_t launch_quantize_act_deflated(int M, int K, int r, int group, const uint16_t* x,
                                         const float* inv_smooth, const uint16_t* L1f, const uint16_t* L1,
-                                        uint8_t* xq, float* xs, uint16_t* t, hipStream_t stream);
+                                        uint8_t* xq, float* xs, uint16_t* t, void* workspace, hipStream_t stream);
 
 // the same two activation kernels with the block Hadamard rotation of Eq. 3
 // (block B, a power of two with 16 <= B <= 1024 dividing K)
 hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bool deflate, const uint16_t* x,
                                        const float* inv_smooth, const uint16_t* L1t, const uint16_t* L1f,
-                                       const uint16_t* L1, uint8_t* xq, float* xs, uint16_t* t,
+                                       const uint16_t* L1, uint8_t* xq, float* xs, uint16_t* t, void* workspace,
                                        hipStream_t stream);
+
+// Few token blocks: K split over workgroups (`splits` of `groups` 64-channel
+// groups each), their partial sums of t in a workspace of act_workspace_bytes
+// (0: the call does not split); the launchers above do so when they get one.
+struct ActSplit {
+  int splits, groups;
+};
+// Split from two workgroups per block on (at most kSplitBlocks blocks), where
+// K is long enough to pay for the second launch (units of four groups; tiles
+// of the rotated kernels).  Graph replays, r = 32, unsplit / split: plain
+// K = 2048 7.4 us (kept), K = 5120 11.9 / 6.9 us, K = 14336 26.4 / 7.7 us (33
+// tokens) and 29.8 / 21.5 us (2048 tokens); deflated K = 1024 11.9 us (kept),
+// K = 5120 43.9 / 12.4 us, K = 14336 117 / 15 us; rotated K = 2048 12.8 / 9.9
+// us, K = 14336 70.6 / 11.3 us; rotated and deflated K = 2048 30.7 / 22.2 us,
+// K = 14336 214 / 24 us (33 tokens) and 218 / 120 us (2048 tokens).
+constexpr int kSplitBlocks = 128;
+constexpr int kMinUnits = 12, kMinUnitsDeflated = 6;
+constexpr int kMinTiles = 2;
+ActSplit act_split(int M, int K, int unit_groups, int min_units);
+ActSplit rotated_split(int M, int K, int r, int B);
+int64_t act_workspace_bytes(int M, int K, int r, int B, bool deflate);
+hipError_t launch_split_t(int M, int r, int splits, const float* part, uint16_t* t, hipStream_t stream);
 
 hipError_t launch_asp_gemm(int M, int N, int K, int r, int group, const uint8_t* xq, const float* xs,
                            const uint16_t* t, const uint8_t* wq, const float* ws, const uint32_t* wsp,

@@ -6,6 +6,8 @@
 //         codes xq [M][K/2] and scales xs [G][M] (Eq. 2), and the rank-r
 //         down-projection t = bf16(x~) . L1 on bf16 matrix cores (V^T x~ of
 //         Eq. 9), all in one pass over x.
+#include <algorithm>
+
 #include "qwam_act.h"
 #include "qwam_device.h"
 #include "qwam_internal.h"
@@ -87,12 +89,18 @@ __global__ __launch_bounds__(256) void inverse_smoothing_kernel(const float* __r
 // below, the 16 waves keep their ranges and store each group's blocks.  The
 // per-wave partial t tiles are summed in LDS in wave order (deterministic) and
 // rounded to bf16 once.
+//
+// With few token blocks (act_split) the workgroup takes a part of K instead,
+// and its sums of t go to a workspace that split_t_kernel adds up: one
+// workgroup's reads of x and L1 (28 KB + 64 bytes of L1 per channel and 16
+// tokens) are what a call of a few tokens waits for, at about 50 B/ns per CU
+// (33 tokens, K = 14336: 26.4 us in three workgroups, 7.7 us in 168).
 // ---------------------------------------------------------------------------
 template <int RANK, bool INV_LDS>
 __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
     const uint16_t* __restrict__ x, const float* __restrict__ inv_smooth,
     const uint16_t* __restrict__ L1f, uint8_t* __restrict__ xq, float* __restrict__ xs,
-    uint16_t* __restrict__ t, int M, int K, int groups_per_wave, int g32) {
+    uint16_t* __restrict__ t, float* __restrict__ part, int M, int K, int groups_per_wg, int groups_per_wave, int g32) {
   constexpr int RB = RANK / 16;
   // dynamic LDS: [nwaves][16][RANK] partial t, then (INV_LDS) [nwaves][groups_per_wave * 64] 1/lambda,
   // then [nwaves][16 rows][128 bytes] code lines
@@ -106,8 +114,10 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
   const int m0 = blockIdx.x * 16;
   const int rows = min(16, M - m0);
   const int G = K / kGroup;
-  const int g_begin = wave * groups_per_wave;
-  const int g_end = min(G, g_begin + groups_per_wave);
+  // the workgroup's groups (all of K, or split blockIdx.y), then the wave's
+  const int wg_begin = static_cast<int>(blockIdx.y) * groups_per_wg;
+  const int g_begin = wg_begin + wave * groups_per_wave;
+  const int g_end = min(min(G, wg_begin + groups_per_wg), g_begin + groups_per_wave);
 
   // the workgroup's 16 rows of x, xq; out-of-range rows read as zero / are dropped
   const buf_rsrc x_rsrc = make_rsrc(x + static_cast<int64_t>(m0) * K, static_cast<uint32_t>(rows) * K * 2u);
@@ -191,7 +201,20 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
 
   store_t_partials<RB>(red, wave, lane, acc);
   __syncthreads();
-  reduce_t<RANK>(red, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, static_cast<float*>(nullptr));
+  if (part != nullptr) store_split_t<RANK>(red, nwaves, m0, part);
+  else reduce_t<RANK>(red, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, static_cast<float*>(nullptr));
+}
+
+// t of a call whose K was split over workgroups: the splits' partial sums
+// (part [splits][stride], stride = padded tokens x r) added in split order.
+__global__ __launch_bounds__(64) void split_t_kernel(const float* __restrict__ part, uint16_t* __restrict__ t, int n,
+                                                     int splits, int stride) {
+  const int e = blockIdx.x * 64 + threadIdx.x;
+  if (e >= n) return;
+  float sum = 0.0f;
+#pragma unroll 8
+  for (int s = 0; s < splits; ++s) sum += part[static_cast<int64_t>(s) * stride + e];
+  t[e] = static_cast<uint16_t>(f32_to_bf16_rne(sum));
 }
 
 // ---------------------------------------------------------------------------
@@ -208,14 +231,18 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
 //  2. every wave walks its groups again: the re-read, re-smoothed x~ goes
 //     through r rank-1 updates on the FP32 matrix cores (deflate_step), whose
 //     result is in the quantizer's lane layout.
+// With few token blocks the phases are launches of their own, each over parts
+// of K (Phase::kSums, kCodes): the second adds the first one's sums in split
+// order (33 tokens, K = 14336: 117 us in one launch, 15 us in two).
 // ---------------------------------------------------------------------------
-template <int RANK, bool INV_LDS>
+template <int RANK, bool INV_LDS, Phase PHASE>
 __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_deflated_kernel(
     const uint16_t* __restrict__ x, const float* __restrict__ inv_smooth,
     const uint16_t* __restrict__ L1f, const uint16_t* __restrict__ L1, uint8_t* __restrict__ xq, float* __restrict__ xs,
-    uint16_t* __restrict__ t, int M, int K, int groups_per_wave, int g32) {
+    uint16_t* __restrict__ t, double* __restrict__ part, int M, int K, int groups_per_wg, int groups_per_wave,
+    int g32) {
   constexpr int RB = RANK / 16;
-  // dynamic LDS: [nwaves][16][RANK] double partial t | [16][RANK] float -t |
+  // dynamic LDS: [nwaves][16][RANK] double partial t (not in kCodes) | [16][RANK] float -t |
   // (INV_LDS) [nwaves][groups_per_wave * 64] 1/lambda
   extern __shared__ double red64[];
 
@@ -227,15 +254,16 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_deflated_
   const int m0 = blockIdx.x * 16;
   const int rows = min(16, M - m0);
   const int G = K / kGroup;
-  const int g_begin = wave * groups_per_wave;
-  const int g_end = min(G, g_begin + groups_per_wave);
+  const int wg_begin = static_cast<int>(blockIdx.y) * groups_per_wg;
+  const int g_begin = wg_begin + wave * groups_per_wave;
+  const int g_end = min(min(G, wg_begin + groups_per_wg), g_begin + groups_per_wave);
 
   const buf_rsrc x_rsrc = make_rsrc(x + static_cast<int64_t>(m0) * K, static_cast<uint32_t>(rows) * K * 2u);
   const buf_rsrc q_rsrc = make_rsrc(xq + static_cast<int64_t>(m0) * (K / 2), static_cast<uint32_t>(rows) * (K / 2));
   const uint32_t x_off = static_cast<uint32_t>(row * K + chunk * 16) * 2u;
   const uint32_t q_off = static_cast<uint32_t>(row * (K / 2) + chunk * 8);
 
-  float* tneg = reinterpret_cast<float*>(red64 + nwaves * 16 * RANK);
+  float* tneg = reinterpret_cast<float*>(red64 + (PHASE == Phase::kCodes ? 0 : nwaves * 16 * RANK));
   float* inv_w = tneg + 16 * RANK + wave * groups_per_wave * kGroup;
   if (INV_LDS && g_begin < g_end) {
     const int n4 = (g_end - g_begin) * (kGroup / 4);
@@ -248,35 +276,43 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_deflated_
   };
 
   // ---- phase 1: t in double ----
-  auto fetch1 = [&](int g, ActFetch<RANK>& f) __attribute__((always_inline)) {
-    const uint32_t go = static_cast<uint32_t>(g) * kGroup * 2u;
-    f.xa = buf_load16(x_rsrc, x_off + go);
-    f.xb = buf_load16(x_rsrc, x_off + go + 16u);
-    load_l1_fragments<RB>(L1f, g, lane, f.l1);
-  };
-  v4d acc[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) acc[rb] = v4d{0.0, 0.0, 0.0, 0.0};
-  auto work1 = [&](int g, const ActFetch<RANK>& f) __attribute__((always_inline)) {
-    float v[16];
-    smooth16(f.xa, f.xb, inv_ptr(g), v);
-    t_step_f64<RB>(v, f.l1, acc);
-  };
-  if (g_begin < g_end) {
-    ActFetch<RANK> fa, fb;
-    fetch1(g_begin, fa);
-    int g = g_begin;
-    for (; g + 1 < g_end; g += 2) {
-      fetch1(g + 1, fb);
-      work1(g, fa);
-      fetch1(min(g + 2, g_end - 1), fa);
-      work1(g + 1, fb);
+  if constexpr (PHASE != Phase::kCodes) {
+    auto fetch1 = [&](int g, ActFetch<RANK>& f) __attribute__((always_inline)) {
+      const uint32_t go = static_cast<uint32_t>(g) * kGroup * 2u;
+      f.xa = buf_load16(x_rsrc, x_off + go);
+      f.xb = buf_load16(x_rsrc, x_off + go + 16u);
+      load_l1_fragments<RB>(L1f, g, lane, f.l1);
+    };
+    v4d acc[RB];
+  #pragma unroll
+    for (int rb = 0; rb < RB; ++rb) acc[rb] = v4d{0.0, 0.0, 0.0, 0.0};
+    auto work1 = [&](int g, const ActFetch<RANK>& f) __attribute__((always_inline)) {
+      float v[16];
+      smooth16(f.xa, f.xb, inv_ptr(g), v);
+      t_step_f64<RB>(v, f.l1, acc);
+    };
+    if (g_begin < g_end) {
+      ActFetch<RANK> fa, fb;
+      fetch1(g_begin, fa);
+      int g = g_begin;
+      for (; g + 1 < g_end; g += 2) {
+        fetch1(g + 1, fb);
+        work1(g, fa);
+        fetch1(min(g + 2, g_end - 1), fa);
+        work1(g + 1, fb);
+      }
+      if (g < g_end) work1(g, fa);
     }
-    if (g < g_end) work1(g, fa);
+    store_t_partials<RB>(red64, wave, lane, acc);
+    __syncthreads();
+    if constexpr (PHASE == Phase::kSums) {
+      store_split_t<RANK>(red64, nwaves, m0, part);
+      return;
+    }
+    reduce_t<RANK>(red64, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, tneg);
+  } else {
+    combine_split_t<RANK>(part, gridDim.y, m0, rows, t + static_cast<int64_t>(m0) * RANK, tneg);
   }
-  store_t_partials<RB>(red64, wave, lane, acc);
-  __syncthreads();
-  reduce_t<RANK>(red64, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, tneg);
   __syncthreads();
 
   // ---- phase 2: deflate with r rank-1 updates, then quantize ----
@@ -321,13 +357,45 @@ hipError_t launch_pack_weights(int K, int N, int group, const float* R, const fl
   return hipGetLastError();
 }
 
+// Splits of K over workgroups, and groups per split, for few token blocks: as
+// many splits as fill the chip once, in whole line chunks of four groups (0
+// splits: K stays whole).
+ActSplit act_split(int M, int K, int unit_groups, int min_units) {
+  const int blocks = (M + 15) / 16;
+  const int units = (K / kGroup + unit_groups - 1) / unit_groups;
+  if (blocks > kSplitBlocks || units < min_units) return {0, 0};
+  const int want = 256 / blocks;                       // >= 2
+  // units per split; at most 128 groups, so that a split's 1/lambda fits in LDS
+  const int per = std::min((units + want - 1) / want, 128 / unit_groups);
+  return {(units + per - 1) / per, per * unit_groups};
+}
+
+static int64_t split_bytes(const ActSplit& s, int M, int r, size_t elem) {
+  return static_cast<int64_t>(s.splits) * ((M + 15) / 16 * 16) * r * static_cast<int64_t>(elem);
+}
+
+int64_t act_workspace_bytes(int M, int K, int r, int B, bool deflate) {
+  const ActSplit s = B != 0 ? rotated_split(M, K, r, B)
+                            : act_split(M, K, 4, deflate ? kMinUnitsDeflated : kMinUnits);
+  return s.splits > 1 ? split_bytes(s, M, r, deflate ? sizeof(double) : sizeof(float)) : 0;
+}
+
+hipError_t launch_split_t(int M, int r, int splits, const float* part, uint16_t* t, hipStream_t stream) {
+  const int n = M * r, stride = (M + 15) / 16 * 16 * r;
+  hipLaunchKernelGGL(split_t_kernel, dim3((n + 63) / 64), dim3(64), 0, stream, part, t, n, splits, stride);
+  return hipGetLastError();
+}
+
 hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x, const float* inv_smooth,
-                               const uint16_t* L1f, uint8_t* xq, float* xs, uint16_t* t,
+                               const uint16_t* L1f, uint8_t* xq, float* xs, uint16_t* t, void* workspace,
                                hipStream_t stream) {
   const int g32 = group == 32 ? 1 : 0;
-  const int G = K / kGroup;
-  // 1/lambda is staged in LDS when the slice fits (K <= 16384); larger K reads it from global memory
-  const bool inv_lds = K <= 16384;
+  const ActSplit split = workspace != nullptr ? act_split(M, K, 4, kMinUnits) : ActSplit{0, 0};
+  float* part = split.splits > 1 ? static_cast<float*>(workspace) : nullptr;
+  const int nsplit = part != nullptr ? split.splits : 1;
+  const int G = part != nullptr ? split.groups : K / kGroup;     // groups per workgroup
+  // 1/lambda is staged in LDS when the slice fits (16384 channels); a longer one is read from global memory
+  const bool inv_lds = G * kGroup <= 16384;
   auto go = [&](auto kernel_lds, auto kernel_global, int max_waves) {
     int nwaves = G < max_waves ? G : max_waves;
     int gpw = (G + nwaves - 1) / nwaves;
@@ -343,13 +411,10 @@ hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x
       const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
       if (e != hipSuccess) return e;
     }
-    if (inv_lds)
-      hipLaunchKernelGGL(kernel_lds, dim3((M + 15) / 16), dim3(64 * nwaves), lds, stream, x, inv_smooth, L1f,
-                         xq, xs, t, M, K, gpw, g32);
-    else
-      hipLaunchKernelGGL(kernel_global, dim3((M + 15) / 16), dim3(64 * nwaves), lds, stream, x, inv_smooth, L1f,
-                         xq, xs, t, M, K, gpw, g32);
-    return hipGetLastError();
+    hipLaunchKernelGGL((inv_lds ? kernel_lds : kernel_global), dim3((M + 15) / 16, nsplit), dim3(64 * nwaves), lds, stream,
+                       x, inv_smooth, L1f, xq, xs, t, part, M, K, G, gpw, g32);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || part == nullptr ? e : launch_split_t(M, r, nsplit, part, t, stream);
   };
   switch (r) {
     case 16: return go(quantize_act_kernel<16, true>, quantize_act_kernel<16, false>, act_waves<16>());
@@ -362,35 +427,44 @@ hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x
 
 hipError_t launch_quantize_act_deflated(int M, int K, int r, int group, const uint16_t* x,
                                         const float* inv_smooth, const uint16_t* L1f, const uint16_t* L1,
-                                        uint8_t* xq, float* xs, uint16_t* t, hipStream_t stream) {
+                                        uint8_t* xq, float* xs, uint16_t* t, void* workspace, hipStream_t stream) {
   const int g32 = group == 32 ? 1 : 0;
-  const int G = K / kGroup;
-  const bool inv_lds = K <= 16384;
-  auto go = [&](auto kernel_lds, auto kernel_global, int max_waves) {
+  const ActSplit split = workspace != nullptr ? act_split(M, K, 4, kMinUnitsDeflated) : ActSplit{0, 0};
+  double* part = split.splits > 1 ? static_cast<double*>(workspace) : nullptr;
+  const int nsplit = part != nullptr ? split.splits : 1;
+  const int G = part != nullptr ? split.groups : K / kGroup;     // groups per workgroup
+  const bool inv_lds = G * kGroup <= 16384;
+  auto go = [&](auto kernel, int max_waves, bool sums) {
     const int nwaves = G < max_waves ? G : max_waves;
     const int gpw = (G + nwaves - 1) / nwaves;
-    const size_t lds = static_cast<size_t>(nwaves) * 16 * r * sizeof(double) + 16 * r * sizeof(float) +
+    const size_t lds = (sums ? static_cast<size_t>(nwaves) * 16 * r * sizeof(double) : 0) + 16 * r * sizeof(float) +
                        (inv_lds ? static_cast<size_t>(nwaves) * gpw * kGroup * sizeof(float) : 0);
     if (lds > 64 * 1024) {
-      const void* fn = inv_lds ? reinterpret_cast<const void*>(kernel_lds) : reinterpret_cast<const void*>(kernel_global);
-      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
       if (e != hipSuccess) return e;
     }
-    if (inv_lds)
-      hipLaunchKernelGGL(kernel_lds, dim3((M + 15) / 16), dim3(64 * nwaves), lds, stream, x, inv_smooth, L1f,
-                         L1, xq, xs, t, M, K, gpw, g32);
-    else
-      hipLaunchKernelGGL(kernel_global, dim3((M + 15) / 16), dim3(64 * nwaves), lds, stream, x, inv_smooth, L1f,
-                         L1, xq, xs, t, M, K, gpw, g32);
+    hipLaunchKernelGGL(kernel, dim3((M + 15) / 16, nsplit), dim3(64 * nwaves), lds, stream, x, inv_smooth, L1f, L1, xq,
+                       xs, t, part, M, K, G, gpw, g32);
     return hipGetLastError();
   };
+#define QWAM_DEFL_CASE(R)                                                                                          \
+  case R: {                                                                                                        \
+    if (part == nullptr)                                                                                           \
+      return inv_lds ? go(quantize_act_deflated_kernel<R, true, Phase::kAll>, act_waves<R>(), true)                \
+                     : go(quantize_act_deflated_kernel<R, false, Phase::kAll>, act_waves<R>(), true);              \
+    /* a split's slice of 1/lambda always fits in LDS */                                                           \
+    const hipError_t e = go(quantize_act_deflated_kernel<R, true, Phase::kSums>, act_waves<R>(), true);            \
+    return e != hipSuccess ? e : go(quantize_act_deflated_kernel<R, true, Phase::kCodes>, act_waves<R>(), false);  \
+  }
   switch (r) {
-    case 16: return go(quantize_act_deflated_kernel<16, true>, quantize_act_deflated_kernel<16, false>, act_waves<16>());
-    case 32: return go(quantize_act_deflated_kernel<32, true>, quantize_act_deflated_kernel<32, false>, act_waves<32>());
-    case 48: return go(quantize_act_deflated_kernel<48, true>, quantize_act_deflated_kernel<48, false>, act_waves<48>());
-    case 64: return go(quantize_act_deflated_kernel<64, true>, quantize_act_deflated_kernel<64, false>, act_waves<64>());
+    QWAM_DEFL_CASE(16)
+    QWAM_DEFL_CASE(32)
+    QWAM_DEFL_CASE(48)
+    QWAM_DEFL_CASE(64)
     default: return hipErrorInvalidValue;
   }
+#undef QWAM_DEFL_CASE
 }
 
 }  // namespace qwam

@@ -18,6 +18,9 @@
 //             of qwam_act.h and runs the plain kernel's per-group steps (or,
 //             deflated, the two phases of the deflated kernel, rotating the
 //             tiles again in phase 2).
+// With few token blocks a workgroup takes some of the tiles (rotated_split):
+// the sums of t are then added by a second launch, which for the deflated
+// variant is the one that deflates and quantizes (Phase::kCodes).
 #include <cmath>
 #include <type_traits>
 
@@ -95,11 +98,13 @@ constexpr int per_wave() { return 16 / act_waves<RANK>(); }
 // operations only, so prefetched global loads stay in flight across it.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int RANK, bool DEFLATE>
+template <int RANK, bool DEFLATE, Phase PHASE>
 __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_kernel(
     const uint16_t* __restrict__ x, const float* __restrict__ inv_smooth,
     const uint16_t* __restrict__ L1f, const uint16_t* __restrict__ L1, uint8_t* __restrict__ xq, float* __restrict__ xs,
-    uint16_t* __restrict__ t, int M, int K, int logB, int T, float hscale, int g32, int red_off) {
+    uint16_t* __restrict__ t, std::conditional_t<DEFLATE, double, float>* __restrict__ part, int M, int K, int logB,
+    int T, float hscale, int g32, int red_off, int tiles_per_wg) {
+  static_assert(DEFLATE || PHASE == Phase::kAll, "one launch without deflation");
   constexpr int RB = RANK / 16;
   constexpr int kMaxPerWave = per_wave<RANK>();
   using Acc = std::conditional_t<DEFLATE, double, float>;
@@ -117,12 +122,13 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
   const int m0 = blockIdx.x * 16;
   const int rows = min(16, M - m0);
   const int TS = T + kTilePad;
-  const int ntiles = K / T;
+  const int tile0 = static_cast<int>(blockIdx.y) * tiles_per_wg;   // the workgroup's tiles (all of them, or a split)
+  const int ntiles = min(K / T - tile0, tiles_per_wg);
   const int npass = T / kGroup;          // 1024-element passes per tile = groups per tile
 
   float* tiles = reinterpret_cast<float*>(lds_raw);
   Acc* red = reinterpret_cast<Acc*>(tiles + red_off);
-  float* tneg = reinterpret_cast<float*>(red + nwaves * 16 * RANK);
+  float* tneg = reinterpret_cast<float*>(red + (PHASE == Phase::kCodes ? 0 : nwaves * 16 * RANK));
   if (red_off < 2 * 16 * TS) tneg = tiles + 2 * 16 * TS;   // red over a tile buffer
 
   const buf_rsrc x_rsrc = make_rsrc(x + static_cast<int64_t>(m0) * K, static_cast<uint32_t>(rows) * K * 2u);
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
       const int p = wave + k * nwaves;
       if (p < npass) {
         const int e = p * 1024 + 16 * lane;
-        const int ch = tb * T + e % T;
+        const int ch = (tile0 + tb) * T + e % T;
         const uint32_t xo = static_cast<uint32_t>((e / T) * K + ch) * 2u;
         rf[k].xa = buf_load16(x_rsrc, xo);
         rf[k].xb = buf_load16(x_rsrc, xo + 16u);
@@ -180,47 +186,55 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) acc[rb] = {};
 
+  RotFetch rf[kMaxPerWave];
+  fetch_tile(0, rf);
   // pass over the tiles: t partials (and, without deflation, the codes).  The
   // next tile's x and 1/lambda are requested as soon as this tile's are in LDS.
   // Tile tb goes to buffer tb % 2, so one barrier per tile suffices: a wave
   // writes buffer tb % 2 only after the barrier of tile tb - 1, which every
   // wave reaches after its reads of tile tb - 2 from that buffer.
-  RotFetch rf[kMaxPerWave];
-  fetch_tile(0, rf);
-  for (int tb = 0; tb < ntiles; ++tb) {
-    float* tile = tiles + (tb & 1) * 16 * TS;
-    rotate_tile(rf, tile);
-    if (tb + 1 < ntiles) fetch_tile(tb + 1, rf);
-    v8s l1[kMaxPerWave][RB][2];
-#pragma unroll
-    for (int k = 0; k < kMaxPerWave; ++k) {
-      const int gl = wave + k * nwaves;
-      if (gl < npass) load_l1_fragments<RB>(L1f, tb * npass + gl, lane, l1[k]);
-    }
-    lds_sync();
-#pragma unroll
-    for (int k = 0; k < kMaxPerWave; ++k) {
-      const int gl = wave + k * nwaves;
-      if (gl < npass) {
-        float v[16];
-        read_group(tile, gl, v);
-        if constexpr (DEFLATE) {
-          t_step_f64<RB>(v, l1[k], acc);
-        } else {
-          store_codes(tb * npass + gl, v);
-          t_step_bf16<RB>(v, l1[k], acc);
+  if constexpr (PHASE != Phase::kCodes) {
+    for (int tb = 0; tb < ntiles; ++tb) {
+      float* tile = tiles + (tb & 1) * 16 * TS;
+      rotate_tile(rf, tile);
+      if (tb + 1 < ntiles) fetch_tile(tb + 1, rf);
+      v8s l1[kMaxPerWave][RB][2];
+  #pragma unroll
+      for (int k = 0; k < kMaxPerWave; ++k) {
+        const int gl = wave + k * nwaves;
+        if (gl < npass) load_l1_fragments<RB>(L1f, (tile0 + tb) * npass + gl, lane, l1[k]);
+      }
+      lds_sync();
+  #pragma unroll
+      for (int k = 0; k < kMaxPerWave; ++k) {
+        const int gl = wave + k * nwaves;
+        if (gl < npass) {
+          float v[16];
+          read_group(tile, gl, v);
+          if constexpr (DEFLATE) {
+            t_step_f64<RB>(v, l1[k], acc);
+          } else {
+            store_codes((tile0 + tb) * npass + gl, v);
+            t_step_bf16<RB>(v, l1[k], acc);
+          }
         }
       }
     }
+    // the second pass takes the last tile first, still in LDS from the first
+    // pass, then tiles 0 .. ntiles - 2 again; tile 0's x is requested here
+    if constexpr (DEFLATE && PHASE == Phase::kAll)
+      if (ntiles > 1) fetch_tile(0, rf);
+    lds_sync();                                   // the partials may overwrite a tile buffer
+    store_t_partials<RB>(red, wave, lane, acc);
+    lds_sync();
+    if (PHASE == Phase::kSums || (!DEFLATE && part != nullptr)) {
+      store_split_t<RANK>(red, nwaves, m0, part);
+      return;
+    }
+    reduce_t<RANK>(red, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, DEFLATE ? tneg : nullptr);
+  } else {
+    combine_split_t<RANK>(part, gridDim.y, m0, rows, t + static_cast<int64_t>(m0) * RANK, tneg);
   }
-  // the second pass takes the last tile first, still in LDS from the first
-  // pass, then tiles 0 .. ntiles - 2 again; tile 0's x is requested here
-  if constexpr (DEFLATE)
-    if (ntiles > 1) fetch_tile(0, rf);
-  lds_sync();                                   // the partials may overwrite a tile buffer
-  store_t_partials<RB>(red, wave, lane, acc);
-  lds_sync();
-  reduce_t<RANK>(red, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, DEFLATE ? tneg : nullptr);
 
   if constexpr (DEFLATE) {
     lds_sync();
@@ -231,19 +245,22 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
     // step i - 2, before the previous barrier.
     const int a_ch = deflate_channel(lane);
     const float* tn_row = tneg + row * RANK;
+    // (A launch of its own for the codes, kCodes, has no tile in LDS: it
+    // rotates tiles 0, 1, .. in order.)
+    constexpr bool kept = PHASE == Phase::kAll;
     const int Lb = (ntiles - 1) & 1;
     for (int i = 0; i < ntiles; ++i) {
-      const int tb = i == 0 ? ntiles - 1 : i - 1;
+      const int tb = !kept ? i : i == 0 ? ntiles - 1 : i - 1;
       float* tile = tiles + ((Lb + i) & 1) * 16 * TS;
-      if (i > 0) {
+      if (!kept || i > 0) {
         rotate_tile(rf, tile);
-        if (i < ntiles - 1) fetch_tile(i, rf);
+        if (tb + 1 < (kept ? ntiles - 1 : ntiles)) fetch_tile(tb + 1, rf);
       }
       uint32_t l1w[kMaxPerWave][RANK / 2];
 #pragma unroll
       for (int k = 0; k < kMaxPerWave; ++k) {
         const int gl = wave + k * nwaves;
-        if (gl < npass) load_l1_row<RANK>(L1, (tb * npass + gl) * kGroup + a_ch, l1w[k]);
+        if (gl < npass) load_l1_row<RANK>(L1, ((tile0 + tb) * npass + gl) * kGroup + a_ch, l1w[k]);
       }
       lds_sync();
 #pragma unroll
@@ -253,7 +270,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
           float v[16];
           read_group(tile, gl, v);
           deflate_step<RANK>(v, l1w[k], tn_row);
-          store_codes(tb * npass + gl, v);
+          store_codes((tile0 + tb) * npass + gl, v);
         }
       }
     }
@@ -465,9 +482,18 @@ static int rotate_tile_width(int K, int B) {
   return base;
 }
 
+// few tokens: one workgroup per token (r = 16 up to K = 2048, r = 32 up to K = 1024)
+static bool rotate_few(int M, int K, int r) { return M <= kFewTokens && (r == 16 || r == 32) && K * r <= 256 * 128; }
+
+ActSplit rotated_split(int M, int K, int r, int B) {
+  if (rotate_few(M, K, r)) return {0, 0};
+  const int T = rotate_tile_width(K, B);
+  return act_split(M, K, T / kGroup, kMinTiles);
+}
+
 hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bool deflate, const uint16_t* x,
                                        const float* inv_smooth, const uint16_t* L1t, const uint16_t* L1f,
-                                       const uint16_t* L1, uint8_t* xq, float* xs, uint16_t* t,
+                                       const uint16_t* L1, uint8_t* xq, float* xs, uint16_t* t, void* workspace,
                                        hipStream_t stream) {
   int logB = 0;
   while ((1 << logB) < B) ++logB;
@@ -476,8 +502,7 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
   // a tile has at most 16 passes / groups: per_wave<r>() per wave
   if (T / kGroup > 16) return hipErrorInvalidValue;
   const float hscale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(B)));
-  // few tokens: one workgroup per token (r = 16 up to K = 2048, r = 32 up to K = 1024)
-  if (M <= kFewTokens && (r == 16 || r == 32) && K * r <= 256 * 128) {
+  if (rotate_few(M, K, r)) {
     auto few = [&](auto kernel) {
       const size_t lds = static_cast<size_t>(K + 256) * sizeof(double) + static_cast<size_t>(K + r) * sizeof(float);
       hipLaunchKernelGGL(kernel, dim3(M), dim3(256), lds, stream, x, inv_smooth, L1t, L1, xq, xs, t, M, K, logB,
@@ -493,16 +518,20 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
     QWAM_FEW(32, 256) QWAM_FEW(32, 512) QWAM_FEW(32, 1024)
 #undef QWAM_FEW
   }
-  auto go = [&](auto kernel, int nwaves, size_t acc_bytes) {
-    // two tiles, then the partial t tiles, or those over a tile buffer when
-    // all of it would not fit in LDS (and they fit in a tile)
+  const ActSplit split = workspace != nullptr ? rotated_split(M, K, r, B) : ActSplit{0, 0};
+  const bool splits = split.splits > 1;
+  const int tiles_per_wg = splits ? split.groups * kGroup / T : K / T;
+  auto go = [&](auto kernel, int nwaves, auto* part, bool sums) {
+    // two tiles, then the partial t tiles (not in the launch of the codes
+    // alone), or those over a tile buffer when all of it would not fit in LDS
+    // (and they fit in a tile)
     const size_t tile_bytes = static_cast<size_t>(16) * (T + kTilePad) * sizeof(float);
-    const size_t red_bytes = static_cast<size_t>(nwaves) * 16 * r * acc_bytes;
+    const size_t red_bytes = sums ? static_cast<size_t>(nwaves) * 16 * r * sizeof(*part) : 0;
     const size_t tneg_bytes = deflate ? 16 * r * sizeof(float) : 0;
     const bool over = 2 * tile_bytes + red_bytes + tneg_bytes > 160 * 1024 && red_bytes <= tile_bytes;
     // over a tile: the buffer the last tile does not use (the deflated
     // variant's second pass reads that tile again)
-    const int last_buf = (K / T - 1) & 1;
+    const int last_buf = (tiles_per_wg - 1) & 1;
     const int red_off = static_cast<int>((over ? 1 - last_buf : 2) * tile_bytes / sizeof(float));
     const size_t lds = 2 * tile_bytes + (over ? 0 : red_bytes) + tneg_bytes;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
@@ -511,14 +540,23 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3((M + 15) / 16), dim3(64 * nwaves), lds, stream, x, inv_smooth, L1f, L1, xq, xs, t,
-                       M, K, logB, T, hscale, group == 32 ? 1 : 0, red_off);
+    hipLaunchKernelGGL(kernel, dim3((M + 15) / 16, splits ? split.splits : 1), dim3(64 * nwaves), lds, stream, x, inv_smooth,
+                       L1f, L1, xq, xs, t, splits ? part : nullptr, M, K, logB, T, hscale, group == 32 ? 1 : 0, red_off,
+                       tiles_per_wg);
     return hipGetLastError();
   };
-#define QWAM_ROT_CASE(R)                                                                            \
-  case R:                                                                                           \
-    return deflate ? go(quantize_act_rotated_kernel<R, true>, act_waves<R>(), sizeof(double))       \
-                   : go(quantize_act_rotated_kernel<R, false>, act_waves<R>(), sizeof(float));
+  double* pd = static_cast<double*>(workspace);
+  float* pf = static_cast<float*>(workspace);
+#define QWAM_ROT_CASE(R)                                                                                            \
+  case R: {                                                                                                         \
+    if (!deflate) {                                                                                                 \
+      const hipError_t e = go(quantize_act_rotated_kernel<R, false, Phase::kAll>, act_waves<R>(), pf, true);        \
+      return e != hipSuccess || !splits ? e : launch_split_t(M, R, split.splits, pf, t, stream);                    \
+    }                                                                                                               \
+    if (!splits) return go(quantize_act_rotated_kernel<R, true, Phase::kAll>, act_waves<R>(), pd, true);            \
+    const hipError_t e = go(quantize_act_rotated_kernel<R, true, Phase::kSums>, act_waves<R>(), pd, true);          \
+    return e != hipSuccess ? e : go(quantize_act_rotated_kernel<R, true, Phase::kCodes>, act_waves<R>(), pd, false);  \
+  }
   switch (r) {
     QWAM_ROT_CASE(16)
     QWAM_ROT_CASE(32)

@@ -11,7 +11,7 @@ take (an explicit stream, or an argument that fails a check) goes through
 ctypes here, which raises for the argument that is wrong.
 
 Names follow the C ABI (include/qwam.h): pack_weights, quantize_act,
-quantize_act_deflated, asp_linear, asp_layer, debug_group_partials,
+quantize_act_deflated (both over qwam_quantize_act_ws), asp_linear, asp_layer, debug_group_partials,
 aog_accumulate, aog_protected_basis; and the measurement probes of include/qwam_probe.h:
 probe_mfma, probe_valu_fma, probe_copy, probe_empty.
 """
@@ -52,6 +52,9 @@ SIGNATURES = {
                                          _c_void_p]),
     "qwam_quantize_act_deflated": (ctypes.c_int, [_LP, _i32, _c_void_p, _c_void_p, _c_void_p,
                                                   _c_void_p, _c_void_p]),
+    "qwam_quantize_act_ws": (ctypes.c_int, [_LP, _i32, _i32, _c_void_p, _c_void_p, _c_void_p, _c_void_p,
+                                            _c_void_p, ctypes.c_int64, _c_void_p]),
+    "qwam_quantize_act_workspace": (ctypes.c_int64, [_LP, _i32, _i32]),
     "qwam_asp_linear": (ctypes.c_int, [_LP, _i32, _c_void_p, _c_void_p, _c_void_p, _c_void_p,
                                        _c_void_p]),
     "qwam_debug_group_partials": (ctypes.c_int, [_LP, _i32, _c_void_p, _c_void_p, _c_void_p]),
@@ -109,7 +112,7 @@ def _native():
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
         mod.bind(*(ctypes.cast(getattr(lib(), f), ctypes.c_void_p).value
-                   for f in ("qwam_quantize_act", "qwam_quantize_act_deflated", "qwam_asp_linear", "qwam_asp_layer")))
+                   for f in ("qwam_quantize_act_ws", "qwam_quantize_act_workspace", "qwam_asp_linear", "qwam_asp_layer")))
         _call = mod
     return _call
 
@@ -228,6 +231,20 @@ def quantize_act_deflated(layer: PackedLayer, x: torch.Tensor, stream=None, out=
     return _quantize(True, "qwam_quantize_act_deflated", layer, x, stream, out)
 
 
+def _workspace(nbytes: int, device, stream) -> Optional[torch.Tensor]:
+    """Device memory for one call on `stream`.  It is taken from the allocator's
+    pool of the stream the call runs on: when it is dropped after the call, the
+    next user of that memory runs behind the call's kernels."""
+    if nbytes <= 0:
+        return None
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        return None                       # a bare stream handle has no pool: the call runs unsplit
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 def _quantize(deflated: bool, name: str, layer: PackedLayer, x: torch.Tensor, stream, out):
     if stream is None:
         done = (_call or _native()).quantize(layer, x, out, deflated)
@@ -244,11 +261,14 @@ def _quantize(deflated: bool, name: str, layer: PackedLayer, x: torch.Tensor, st
     else:
         xq, xs, t = out
     c = layer.c_struct()
-    st = getattr(lib(), name)(
-            ctypes.byref(c), M, _req(x, "x", torch.bfloat16, (M, layer.K)),
-            _req(xq, "xq", torch.uint8, (M, layer.K // 2)),
-            _req(xs, "xs", torch.float32, (layer.K // layer.group, M)),
-            _req(t, "t", torch.bfloat16, (M, layer.r)), _stream_ptr(stream))
+    # few tokens and a large K: the call splits K over workgroups through a workspace
+    need = lib().qwam_quantize_act_workspace(ctypes.byref(c), M, deflated)
+    ws = _workspace(need, dev, stream)
+    st = lib().qwam_quantize_act_ws(ctypes.byref(c), M, deflated, _req(x, "x", torch.bfloat16, (M, layer.K)),
+                                    _req(xq, "xq", torch.uint8, (M, layer.K // 2)),
+                                    _req(xs, "xs", torch.float32, (layer.K // layer.group, M)),
+                                    _req(t, "t", torch.bfloat16, (M, layer.r)),
+                                    None if ws is None else ws.data_ptr(), max(need, 0), _stream_ptr(stream))
     _check(name, st)
     return xq, xs, t
 
