@@ -16,6 +16,15 @@
 //     (lane l: row / column l % 32, half l / 32 of a group, 16 bytes = 32
 //     codes), four groups per chunk, two chunks in flight: with eight waves a
 //     K of 4096 is one memory round trip;
+//   * a longer K (STAGED) comes through LDS instead: each wave copies stages of
+//     four groups (one cache line of every row, eight lanes per line,
+//     buffer_load ... lds) into two buffers of its own, reads a stage into
+//     registers at once and requests its buffer again, with no barrier.  Loads
+//     straight into the operand layout touch each line in four 32-byte pieces,
+//     one chunk after another, and eight waves' 64 rows of lines do not stay
+//     in the 32 KB L1, so each line came from L2 up to four times: at K = 14336,
+//     N = 3072, M = 33 20.3 us, staged 13.0 us (the DPP multiplies and the
+//     updates of two waves per SIMD are about half of that);
 //   * the activation scales are broadcast across each row of 16 lanes by DPP
 //     inside the scale multiply, as in the large-tile kernel;
 //   * group 32 (GS = 32): as in the large-tile kernel, lane half h holds group
@@ -35,6 +44,11 @@ constexpr int SB = 32;             // block edge (rows and columns)
 constexpr int CH = 4;              // groups per chunk
 constexpr int KW = 8;              // waves per block, each a contiguous range of groups
 
+constexpr int STAGE_CODES = 2 * SB * CH * 32;          // a wave's staged codes: SB + SB rows of one line
+
+// slot permutation of the eight 16-byte chunks of a staged row (conflict-free fragment reads)
+__device__ __forceinline__ int small_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
 template <int NS>
 struct Chunk {
   uint4 a[CH], b[CH];              // packed codes of this lane's row / column and half
@@ -43,13 +57,21 @@ struct Chunk {
 
 }  // namespace
 
-template <int RANK, bool PARTIALS, int GS>
+template <int RANK, bool PARTIALS, int GS, bool STAGED>
 __global__ __launch_bounds__(64 * KW) void asp_gemm_small_kernel(
     const uint8_t* __restrict__ xq, const float* __restrict__ xs, const uint16_t* __restrict__ t,
     const uint8_t* __restrict__ wq, const float* __restrict__ ws, const uint16_t* __restrict__ L2t,
     const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, int32_t* __restrict__ P, int M,
     int N, int K) {
-  __shared__ float red[KW][16][64];       // partial blocks of the waves
+  // partial blocks of the waves; staged, each in its wave's first buffer, and
+  // the two buffers are LDS variables of their own (the compiler then keeps
+  // the copies into one apart from the reads of the other)
+  constexpr int STAGE = STAGED ? STAGE_CODES + 2 * SB * CH * (kGroup / GS) * 4 : 16 * 64 * 4;
+  __shared__ __attribute__((aligned(16))) uint8_t st0[KW][STAGE];
+  __shared__ __attribute__((aligned(16))) uint8_t st1[STAGED ? KW : 1][STAGED ? STAGE : 16];
+  auto red = [&](int w, int v, int l) __attribute__((always_inline)) -> float& {
+    return reinterpret_cast<float*>(st0[w])[v * 64 + l];
+  };
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -162,28 +184,81 @@ __global__ __launch_bounds__(64 * KW) void asp_gemm_small_kernel(
     bbits = __builtin_amdgcn_raw_buffer_load_b16(b_rsrc, static_cast<uint32_t>(nt) * 2u, 0, 0);
   }
 
-  // two chunks in flight: chunk c+1 is requested before chunk c is multiplied
-  Chunk<NS> c0, c1;
-  if (NC > 0) load_any(0, c0);
-  for (int c = 0; c < NC; c += 2) {
-    if (c + 1 < NC) load_any(c + 1, c1);
-    process_any(c, c0);
-    if (c + 2 < NC) load_any(c + 2, c0);
-    if (c + 1 < NC) process_any(c + 1, c1);
+  if constexpr (STAGED) {
+    // stage c = chunk c: copy i covers rows 8 i + l/8, slot l%8 (chunk slot ^
+    // swz(row)); scales [NS CH][32] of the tokens, then of the channels, 64
+    // floats (two scale groups) per copy
+    constexpr int OFF_B = STAGE_CODES / 2, OFF_S = STAGE_CODES, NSC = NS * CH;
+    constexpr int NI = 2 * SB / 8 + NSC;                 // copies per stage
+    const int crow = lane >> 3;
+    const uint32_t c_off[2] = {static_cast<uint32_t>(crow * KB + (((lane & 7) ^ small_swz(crow)) * 16)),
+                               static_cast<uint32_t>((crow + 8) * KB + (((lane & 7) ^ small_swz(crow + 8)) * 16))};
+    auto issue = [&](int c, uint8_t* st) __attribute__((always_inline)) {
+      const int g = g_lo + c * CH;
+#pragma unroll
+      for (int i = 0; i < SB / 8; ++i) {
+        const uint32_t off = c_off[i & 1] + static_cast<uint32_t>(16 * (i >> 1)) * KB + static_cast<uint32_t>(g) * 32u;
+        buf_load16_lds(a_rsrc, off, st + i * 1024);
+        buf_load16_lds(b_rsrc, off, st + OFF_B + i * 1024);
+      }
+#pragma unroll
+      for (int i = 0; i < NSC / 2; ++i) {
+        const uint32_t sg = static_cast<uint32_t>(NS * g + 2 * i + fhalf);
+        buf_load4_lds(xs_rsrc, (sg * static_cast<uint32_t>(M) + m0 + frow) * 4u, st + OFF_S + i * 256);
+        buf_load4_lds(ws_rsrc, (sg * static_cast<uint32_t>(N) + n0 + frow) * 4u, st + OFF_S + NSC * 128 + i * 256);
+      }
+    };
+    auto stage = [&](int c, uint8_t* st) __attribute__((always_inline)) {
+      if (c + 1 < NC) wait_vmcnt<NI>();
+      else wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+      Chunk<NS> ch;
+      const float* sc = reinterpret_cast<const float*>(st + OFF_S);
+#pragma unroll
+      for (int q = 0; q < CH; ++q) {
+        const int slot = (((2 * q) | fhalf) ^ small_swz(frow)) * 16;
+        ch.a[q] = *reinterpret_cast<const uint4*>(st + frow * 128 + slot);
+        ch.b[q] = *reinterpret_cast<const uint4*>(st + OFF_B + frow * 128 + slot);
+#pragma unroll
+        for (int h = 0; h < NS; ++h) {
+          ch.sx[q][h] = sc[(NS * q + h) * 32 + sx_row];
+          ch.sw[q][h] = sc[NSC * 32 + (NS * q + h) * 32 + frow];
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (c + 2 < NC) issue(c + 2, st);
+      process_any(c, ch);
+    };
+    if (NC > 0) issue(0, st0[wave]);
+    if (NC > 1) issue(1, st1[wave]);
+    for (int c = 0; c < NC; c += 2) {
+      stage(c, st0[wave]);
+      if (c + 1 < NC) stage(c + 1, st1[wave]);
+    }
+  } else {
+    // two chunks in flight: chunk c+1 is requested before chunk c is multiplied
+    Chunk<NS> c0, c1;
+    if (NC > 0) load_any(0, c0);
+    for (int c = 0; c < NC; c += 2) {
+      if (c + 1 < NC) load_any(c + 1, c1);
+      process_any(c, c0);
+      if (c + 2 < NC) load_any(c + 2, c0);
+      if (c + 1 < NC) process_any(c + 1, c1);
+    }
   }
   if (PARTIALS) return;
 
   // partial blocks -> LDS, summed in wave order: wave w finishes result
   // registers v0 = 2w and v0 + 1 (token 8(v/4) + 4(l/32) + v%4, column l%32)
 #pragma unroll
-  for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
+  for (int v = 0; v < 16; ++v) red(wave, v, lane) = acc[v];
   __syncthreads();
   const int v0 = 2 * wave;
   float c2[2] = {0.0f, 0.0f};
 #pragma unroll
   for (int w = 0; w < KW; ++w)
 #pragma unroll
-    for (int e = 0; e < 2; ++e) c2[e] += red[w][v0 + e][lane];
+    for (int e = 0; e < 2; ++e) c2[e] += red(w, v0 + e, lane);
 
   // ---- epilogue: acc + t . L2 (bf16 MFMA, float32 accumulate) + bias; the
   // other result registers start at zero and are not used ----
@@ -209,31 +284,36 @@ __global__ __launch_bounds__(64 * KW) void asp_gemm_small_kernel(
   }
 }
 
+// Up to this K the operands go straight to registers (a wave has at most two
+// groups there, one round trip); above, through LDS.  Direct / staged, graph
+// replays of four layers: K = 1024, N = 4096, M = 16 4.3 / 4.4 us (group 32
+// 4.6 / 4.8); K = 2048, N = 3072, M = 33 5.7 / 4.8; K = 3072, N = 9216, M = 64
+// 19.0 / 15.9; K = 14336, N = 3072, M = 33 20.3 / 13.0 us.
+constexpr int kDirectK = 1024;
+
 static unsigned small_blocks(int M, int N) {
   return static_cast<unsigned>(((M + SB - 1) / SB) * ((N + SB - 1) / SB));
 }
 
-template <int GS>
+template <int GS, bool STAGED>
 static hipError_t launch_small_gs(int M, int N, int K, int r, const uint8_t* xq, const float* xs, const uint16_t* t,
                                   const uint8_t* wq, const float* ws, const uint16_t* L2t, const uint16_t* bias,
                                   uint16_t* y, hipStream_t stream) {
   const dim3 grid(small_blocks(M, N)), block(64 * KW);
+#define QWAM_SMALL_CASE(R)                                                                                        \
+  case R:                                                                                                         \
+    hipLaunchKernelGGL((asp_gemm_small_kernel<R, false, GS, STAGED>), grid, block, 0, stream, xq, xs, t, wq, ws,  \
+                       L2t, bias, y, nullptr, M, N, K);                                                           \
+    break;
   switch (r) {
-    case 16:
-      hipLaunchKernelGGL((asp_gemm_small_kernel<16, false, GS>), grid, block, 0, stream, xq, xs, t, wq, ws, L2t, bias, y, nullptr, M, N, K);
-      break;
-    case 32:
-      hipLaunchKernelGGL((asp_gemm_small_kernel<32, false, GS>), grid, block, 0, stream, xq, xs, t, wq, ws, L2t, bias, y, nullptr, M, N, K);
-      break;
-    case 48:
-      hipLaunchKernelGGL((asp_gemm_small_kernel<48, false, GS>), grid, block, 0, stream, xq, xs, t, wq, ws, L2t, bias, y, nullptr, M, N, K);
-      break;
-    case 64:
-      hipLaunchKernelGGL((asp_gemm_small_kernel<64, false, GS>), grid, block, 0, stream, xq, xs, t, wq, ws, L2t, bias, y, nullptr, M, N, K);
-      break;
+    QWAM_SMALL_CASE(16)
+    QWAM_SMALL_CASE(32)
+    QWAM_SMALL_CASE(48)
+    QWAM_SMALL_CASE(64)
     default:
       return hipErrorInvalidValue;
   }
+#undef QWAM_SMALL_CASE
   return hipGetLastError();
 }
 
@@ -241,17 +321,20 @@ hipError_t launch_asp_gemm_small(int M, int N, int K, int r, int group, const ui
                                  const uint16_t* t, const uint8_t* wq, const float* ws,
                                  const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                                  hipStream_t stream) {
-  return group == 32 ? launch_small_gs<32>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream)
-                     : launch_small_gs<64>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream);
+  if (K > kDirectK)
+    return group == 32 ? launch_small_gs<32, true>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream)
+                       : launch_small_gs<64, true>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream);
+  return group == 32 ? launch_small_gs<32, false>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream)
+                     : launch_small_gs<64, false>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream);
 }
 
 hipError_t launch_group_partials_small(int M, int N, int K, int group, const uint8_t* xq, const uint8_t* wq,
                                        int32_t* P, hipStream_t stream) {
   if (group == 32)
-    hipLaunchKernelGGL((asp_gemm_small_kernel<32, true, 32>), dim3(small_blocks(M, N)), dim3(64 * KW), 0, stream, xq,
+    hipLaunchKernelGGL((asp_gemm_small_kernel<32, true, 32, false>), dim3(small_blocks(M, N)), dim3(64 * KW), 0, stream, xq,
                        nullptr, nullptr, wq, nullptr, nullptr, nullptr, nullptr, P, M, N, K);
   else
-    hipLaunchKernelGGL((asp_gemm_small_kernel<32, true, 64>), dim3(small_blocks(M, N)), dim3(64 * KW), 0, stream, xq,
+    hipLaunchKernelGGL((asp_gemm_small_kernel<32, true, 64, false>), dim3(small_blocks(M, N)), dim3(64 * KW), 0, stream, xq,
                        nullptr, nullptr, wq, nullptr, nullptr, nullptr, nullptr, P, M, N, K);
   return hipGetLastError();
 }

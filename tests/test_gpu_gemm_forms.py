@@ -1,6 +1,7 @@
-"""GPU parity of the GEMM for a few hundred tokens (tiles of 32 or 64 tokens x
-64 channels with K split over the workgroup's waves), at the edges of its
-tiles, stages and wave ranges: token remainders of one and tile - 1, N not a
+"""GPU parity of the GEMM's forms for few tokens (up to 64: operands through LDS
+from K = 1088 on) and for a few hundred (tiles of 32 or 64 tokens x 64 channels
+with K split over the workgroup's waves), at the edges of their tiles, stages
+and wave ranges: token remainders of one and tile - 1, N not a
 multiple of the tile, fewer spans than waves, spans that fill no whole stage,
 every rank, both group sizes, with and without a bias.
 
@@ -28,6 +29,10 @@ def _gpu():
 
 
 SHAPES = [
+    (1, 1088, 16, 16, 64, True),       # few tokens, staged: ranges of three groups, the last wave idle
+    (33, 2624, 80, 48, 32, False),     # 41 groups: ranges of six, stages of four and two; one token of block 2
+    (64, 4160, 112, 64, 64, True),     # 65 groups: ranges of nine
+    (17, 14336, 48, 32, 32, False),    # ranges of 28: seven full stages
     # M, K, N, r, group, bias: the form the launcher's estimate picks
     (65, 64, 16, 16, 64, True),        # 32 x 64, four waves: one span, three waves idle, 16 of 64 columns
     (95, 448, 208, 32, 64, False),     # four waves, seven spans (last range one span), 31 of 32 tokens
@@ -40,10 +45,10 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("M,K,N,r,group,bias", SHAPES)
-def test_mid_gemm_parity(M, K, N, r, group, bias):
+def test_gemm_form_parity(M, K, N, r, group, bias):
     d = I.custom(M, K, N, r, seed=17 + M, n_outliers=3, with_bias=bias)
     f = dict(oracle_factors(d), group=group)
-    log(f"  mid GEMM M={M} K={K} N={N} r={r} group={group} bias={bias}")
+    log(f"  GEMM form M={M} K={K} N={N} r={r} group={group} bias={bias}")
     ref = O.asp_linear(d.x, f, bias_bits=d.bias)
     layer = gpu_layer(f, d.bias)
     x, xq, xs, t, y = run_gpu(layer, d.x)
