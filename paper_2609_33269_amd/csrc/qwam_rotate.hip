@@ -9,11 +9,11 @@
 // A block spans several groups, so a workgroup (16 tokens) works in tiles of
 // T channels (a multiple of B and of 64 dividing K, at most 1024):
 //   rotate:   pass p of a tile is 1024 consecutive elements of the [16][T]
-//             tile; lane l holds 16 consecutive channels of one token, so
-//             butterfly stages 0-3 run in registers and stages 4 .. log2(B)-1
-//             between lanes l and l ^ 2^(s-4) (DPP, ds_swizzle and the
-//             permlane swaps of gfx950).  The rotated tile goes to LDS
-//             (rows padded by 4 floats against bank conflicts).
+//             tile; a lane holds 16 consecutive channels of one token, so
+//             butterfly stages 0-3 run in registers and the others between
+//             lanes (fwht16: DPP operands and the permlane swaps of gfx950).
+//             The rotated tile goes to LDS (rows padded by 4 floats and
+//             swizzled against bank conflicts).
 //   quantize: each wave reads its groups of the tile back in the lane layout
 //             of qwam_act.h and runs the plain kernel's per-group steps (or,
 //             deflated, the two phases of the deflated kernel, rotating the
@@ -34,9 +34,52 @@ namespace {
 
 constexpr int kTilePad = 4;   // floats of padding per LDS tile row
 
-// Fast Walsh-Hadamard transform of a block of 2^logB elements held 16 per lane
-// (lane bit b <-> element bit 4 + b): v becomes v H_B, unnormalized.
-__device__ __forceinline__ void fwht16(float (&v)[16], int lane, int logB) {
+// A tile row keeps float4 q of its 16-channel chunk c in slot q ^ tile_swz(c).
+// The rotation writes one float4 per lane, 64 bytes apart: unswizzled, 16
+// lanes fall on 16 of the 64 banks.  The reads (16 rows, one chunk) are
+// conflict-free either way, by the padding.
+__device__ __forceinline__ int tile_swz(int c) { return (c >> 2) & 3; }
+
+// The 1024 elements of a rotation pass are indexed by 10 bits.  Lane l holds
+// 16 consecutive ones, chunk rot_chunk(l) (bits 4-9), register = bits 0-3.
+// Within 8 lanes the chunks are ordered so that chunk bit 2 (element bit 6)
+// pairs lanes l and l ^ 7, which a DPP modifier can reach (row_half_mirror);
+// bits 0, 1, 3 pair l ^ 1, l ^ 2 (quad permutes) and l ^ 8 (row_ror:8).
+__device__ __forceinline__ int rot_chunk(int lane) { return lane ^ ((lane & 4) ? 3 : 0); }
+
+// Fast Walsh-Hadamard transform of blocks of 2^logB elements (stages on
+// element bit 0, 1, .., one rounding per butterfly), times `scale`.  What it
+// costs is vector instructions, so each stage takes as few as it can:
+//   bits 0-3   between the lane's registers, one add or subtraction each;
+//   bits 4-7   between lanes, one v_fmac_f32 with a DPP operand each
+//              (EXACT: two): v <- v + s p, s = -1 in the lane whose element
+//              has the bit set, which so holds b - a instead of a - b.  A lane's
+//              values thus change sign together; the final multiply undoes it.
+//              Negation commutes with rounding, except that the sign of a zero
+//              result is lost: fma(v, scale, +0) makes every zero +0, which is
+//              what the true stages give unless an input is -0 (a -0 comes from -0s only).  EXACT keeps
+//              a - b itself and is for passes that hold a -0;
+//   bits 8, 9  v_permlane16/32_swap of registers i and i + 4 (i + 8): the
+//              lower lanes then hold both halves of register i's pairs and
+//              the upper ones those of register i + 4, so one add and one
+//              subtraction serve two elements.  Register bit 2 (3) and lane bit
+//              4 (5) trade places; rot_element gives the resulting element.
+// 11 vector instructions per element (18 and an LDS swizzle with a separate
+// exchange per element): M = 4096, r = 32, rotated 20.8 -> 17.6 us (K = 3072)
+// and 82 -> 72 us (K = 14336), rotated and deflated 52 -> 45 and 219 -> 186 us.
+//
+// v <- v + s (v of the lane that `ctrl` names), for eight registers in one
+// instruction each (the compiler keeps the exchange and the multiply-add
+// apart).  The leading s_nop separates a register's last write from its use as
+// a DPP source, the trailing one the last writes from a lane swap.
+#define QWAM_FMAC1_DPP(N, CTRL) "v_fmac_f32_dpp %" #N ", %" #N ", %8 " CTRL " row_mask:0xf bank_mask:0xf\n\t"
+#define QWAM_FMAC8_DPP(a, b, c, d, e, f, g, h, s, CTRL)                                                              \
+  asm("s_nop 1\n\t" QWAM_FMAC1_DPP(0, CTRL) QWAM_FMAC1_DPP(1, CTRL) QWAM_FMAC1_DPP(2, CTRL) QWAM_FMAC1_DPP(3, CTRL)  \
+          QWAM_FMAC1_DPP(4, CTRL) QWAM_FMAC1_DPP(5, CTRL) QWAM_FMAC1_DPP(6, CTRL) QWAM_FMAC1_DPP(7, CTRL) "s_nop 1"  \
+      : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(e), "+v"(f), "+v"(g), "+v"(h)                                       \
+      : "v"(s))
+template <bool EXACT>
+__device__ __forceinline__ void fwht16(float (&v)[16], int lane, int logB, float scale) {
 #pragma unroll
   for (int h = 1; h < 16; h <<= 1)
 #pragma unroll
@@ -46,39 +89,66 @@ __device__ __forceinline__ void fwht16(float (&v)[16], int lane, int logB) {
         v[i] = a + b;
         v[i + h] = a - b;
       }
-  // Stages between lanes l and l ^ m.  The partner's value p comes by DPP
-  // (m = 1, 2: quad permutes; m = 8: rotation by 8 inside a row of 16), by
-  // ds_swizzle (m = 4) or by v_permlane16/32_swap (m = 16, 32), instead of a
-  // ds_bpermute per element.  The lane of the pair without bit m gets a + b,
-  // the other a - b, one rounding each: fma(., +-1, .) computes exactly that.
-  for (int s = 4; s < logB; ++s) {
-    const int m = 1 << (s - 4);
-    const float sgn = (lane & m) != 0 ? -1.0f : 1.0f;   // -1: this lane holds the element with bit s set
-    // the lower lane: v + p = a + b; the upper: p - v = a - b
-    auto near = [&](auto xchg) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = __builtin_fmaf(v[i], sgn, __int_as_float(xchg(__float_as_int(v[i]))));
-    };
-    // swap results: [0] = own value in the lower half of each pair of rows
-    // (m = 16) or in lanes 0-31 (m = 32), the partner's in the other; [1]
-    // the reverse.  The lower lane computes [0] + [1] = a + b, the upper
-    // [0] - [1] = a - b.
-    auto far = [&](auto swap) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const auto r = swap(__float_as_uint(v[i]));
-        v[i] = __builtin_fmaf(__uint_as_float(r[1]), sgn, __uint_as_float(r[0]));
-      }
-    };
-    switch (m) {
-      case 1: near([](int u) { return __builtin_amdgcn_update_dpp(0, u, 0xB1, 0xF, 0xF, false); }); break;  // quad_perm [1,0,3,2]
-      case 2: near([](int u) { return __builtin_amdgcn_update_dpp(0, u, 0x4E, 0xF, 0xF, false); }); break;  // quad_perm [2,3,0,1]
-      case 4: near([](int u) { return __builtin_amdgcn_ds_swizzle(u, (4 << 10) | 0x1F); }); break;          // xor 4
-      case 8: near([](int u) { return __builtin_amdgcn_update_dpp(0, u, 0x128, 0xF, 0xF, false); }); break; // row_ror:8
-      case 16: far([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); }); break;
-      default: far([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); }); break;
-    }
+  const int c = rot_chunk(lane);
+  float total = scale;
+#define QWAM_DPP_STAGE(BIT, CTRL, TEXT)                                                                              \
+  if (logB > 4 + BIT) {                                                                                              \
+    const float s = ((c >> BIT) & 1) != 0 ? -1.0f : 1.0f;                                                            \
+    if constexpr (EXACT) {                                                                                           \
+      _Pragma("unroll") for (int i = 0; i < 16; ++i) {                                                               \
+        const int u = __float_as_int(v[i]);                                                                          \
+        v[i] = __builtin_fmaf(v[i], s, __int_as_float(__builtin_amdgcn_update_dpp(0, u, CTRL, 0xF, 0xF, false)));    \
+      }                                                                                                              \
+    } else {                                                                                                         \
+      QWAM_FMAC8_DPP(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], s, TEXT);                                       \
+      QWAM_FMAC8_DPP(v[8], v[9], v[10], v[11], v[12], v[13], v[14], v[15], s, TEXT);                                 \
+      total *= s;                                                                                                    \
+    }                                                                                                                \
   }
+  QWAM_DPP_STAGE(0, 0xB1, "quad_perm:[1,0,3,2]")     // l ^ 1
+  QWAM_DPP_STAGE(1, 0x4E, "quad_perm:[2,3,0,1]")     // l ^ 2
+  QWAM_DPP_STAGE(2, 0x141, "row_half_mirror")        // l ^ 7
+  QWAM_DPP_STAGE(3, 0x128, "row_ror:8")              // l ^ 8
+#undef QWAM_DPP_STAGE
+  auto swap_stage = [&](auto hc, auto swap) __attribute__((always_inline)) {
+    constexpr int h = decltype(hc)::value;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (!(i & h)) {
+        const auto r = swap(__float_as_uint(v[i]), __float_as_uint(v[i + h]));
+        const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+        v[i] = a + b;
+        v[i + h] = a - b;
+      }
+  };
+  if (logB > 8)
+    swap_stage(std::integral_constant<int, 4>{},
+               [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); });
+  if (logB > 9)
+    swap_stage(std::integral_constant<int, 8>{},
+               [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); });
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = EXACT ? v[i] * scale : __builtin_fmaf(v[i], total, 0.0f);
+}
+
+#undef QWAM_FMAC8_DPP
+#undef QWAM_FMAC1_DPP
+
+// The element of the pass that register 4 q (q = 0..3) holds after fwht16
+// (registers 4 q + 1 .. + 3: the next three).
+__device__ __forceinline__ int rot_element(int lane, int q, int logB) {
+  const int c = rot_chunk(lane);
+  const int b2 = q & 1, b3 = q >> 1, l4 = (c >> 4) & 1, l5 = c >> 5;
+  return 16 * (c & 15) + (logB > 8 ? 4 * l4 + 256 * b2 : 4 * b2 + 256 * l4) +
+         (logB > 9 ? 8 * l5 + 512 * b3 : 8 * b3 + 512 * l5);
+}
+
+// Smoothed inputs of a pass that include a -0 (the transform's exact form).
+__device__ __forceinline__ bool any_negative_zero(const float (&v)[16]) {
+  int least = __float_as_int(v[0]);
+#pragma unroll
+  for (int i = 1; i < 16; ++i) least = min(least, __float_as_int(v[i]));
+  return __any(least == INT32_MIN);      // -0 is the least float bit pattern as an integer
 }
 
 }  // namespace
@@ -141,7 +211,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
     for (int k = 0; k < kMaxPerWave; ++k) {
       const int p = wave + k * nwaves;
       if (p < npass) {
-        const int e = p * 1024 + 16 * lane;
+        const int e = p * 1024 + 16 * rot_chunk(lane);
         const int ch = (tile0 + tb) * T + e % T;
         const uint32_t xo = static_cast<uint32_t>((e / T) * K + ch) * 2u;
         rf[k].xa = buf_load16(x_rsrc, xo);
@@ -158,22 +228,32 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
     for (int k = 0; k < kMaxPerWave; ++k) {
       const int p = wave + k * nwaves;
       if (p < npass) {
-        const int e = p * 1024 + 16 * lane;
+        // The lane's signs and addresses do not change from tile to tile.  Kept
+        // in registers (128 at 16 waves) they make the variant without
+        // deflation spill, which then takes 83 instead of 74 us at M = 4096,
+        // K = 14336; the deflated one keeps them (182 against 197 us).
+        int ln = lane;
+        if constexpr (!DEFLATE) asm volatile("" : "+v"(ln));
         float v[16];
         smooth16_regs(rf[k].xa, rf[k].xb, rf[k].inv, v);
-        fwht16(v, lane, logB);
-        float4* dst = reinterpret_cast<float4*>(tile + (e / T) * TS + e % T);
+        if (any_negative_zero(v)) fwht16<true>(v, ln, logB, hscale);
+        else fwht16<false>(v, ln, logB, hscale);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          dst[q] = make_float4(v[4 * q] * hscale, v[4 * q + 1] * hscale, v[4 * q + 2] * hscale, v[4 * q + 3] * hscale);
+        for (int q = 0; q < 4; ++q) {
+          const int e = p * 1024 + rot_element(ln, q, logB);
+          const int ch = e % T;
+          *reinterpret_cast<float4*>(tile + (e / T) * TS + (ch & ~15) + 4 * (((ch >> 2) & 3) ^ tile_swz(ch >> 4))) =
+              make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        }
       }
     }
   };
   auto read_group = [&](const float* tile, int gl, float (&v)[16]) __attribute__((always_inline)) {
-    const float4* src = reinterpret_cast<const float4*>(tile + row * TS + gl * kGroup + chunk * 16);
+    const float* src = tile + row * TS + gl * kGroup + chunk * 16;
+    const int sw = tile_swz(4 * gl + chunk);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const float4 f = src[q];
+      const float4 f = *reinterpret_cast<const float4*>(src + 4 * (q ^ sw));
       v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
     }
   };
@@ -281,8 +361,8 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
 // token, so that a call of a few tokens spreads over as many CUs as tokens
 // instead of running on one.  The same arithmetic as above, laid out for one
 // token:
-//   rotate:   wave w < ceil(K / 1024) transforms channels 1024 w + 16 lane ..
-//             +15 in registers (fwht16) into an LDS row of K floats, and
+//   rotate:   wave w < ceil(K / 1024) transforms channels 1024 w .. + 1023,
+//             16 per lane, in registers (fwht16) into an LDS row of K floats, and
 //             bf16(x~) as doubles into a second row;
 //   t:        thread i sums column j = i % r over its range of CH = KMAX r /
 //             256 consecutive channels in double, from its L1t row segment
@@ -319,7 +399,7 @@ __global__ __launch_bounds__(256) void quantize_act_rotated_few_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = blockIdx.x;
   const int npass = (K + 1023) / 1024;
-  const int e = wave * 1024 + 16 * lane;        // first channel of this lane's rotation slice
+  const int e = wave * 1024 + 16 * rot_chunk(lane);   // first channel of this lane's slice before the rotation
   const bool rot_wave = wave < npass;
   const bool rot_lane = rot_wave && e < K;
   const int tj = tid % RANK;                    // column of t
@@ -368,17 +448,17 @@ __global__ __launch_bounds__(256) void quantize_act_rotated_few_kernel(
   {
     float v[16];
     smooth16_regs(rf.xa, rf.xb, rf.inv, v);
-    fwht16(v, lane, logB);
+    if (any_negative_zero(v)) fwht16<true>(v, lane, logB, hscale);
+    else fwht16<false>(v, lane, logB, hscale);
     if (rot_lane) {
-      float4* dst = reinterpret_cast<float4*>(xt + e);
-      double2* dd = reinterpret_cast<double2*>(xd + e);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float4 f = make_float4(v[4 * q] * hscale, v[4 * q + 1] * hscale, v[4 * q + 2] * hscale,
-                                     v[4 * q + 3] * hscale);
-        dst[q] = f;
-        dd[2 * q] = make_double2(bf16_to_f32(f32_to_bf16_rne(f.x)), bf16_to_f32(f32_to_bf16_rne(f.y)));
-        dd[2 * q + 1] = make_double2(bf16_to_f32(f32_to_bf16_rne(f.z)), bf16_to_f32(f32_to_bf16_rne(f.w)));
+        const int to = wave * 1024 + rot_element(lane, q, logB);
+        const float4 f = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        *reinterpret_cast<float4*>(xt + to) = f;
+        double2* dd = reinterpret_cast<double2*>(xd + to);
+        dd[0] = make_double2(bf16_to_f32(f32_to_bf16_rne(f.x)), bf16_to_f32(f32_to_bf16_rne(f.y)));
+        dd[1] = make_double2(bf16_to_f32(f32_to_bf16_rne(f.z)), bf16_to_f32(f32_to_bf16_rne(f.w)));
       }
     }
   }
