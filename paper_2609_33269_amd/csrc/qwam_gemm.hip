@@ -136,8 +136,16 @@ __device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int& 
 
 }  // namespace
 
-template <int RANK, bool PARTIALS, int GS>
-__global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
+// KSPLIT = 2: eight waves on one tile and one workgroup per CU, the two groups
+// of four waves each running the same pipeline over half of the ring stages
+// with LDS stages of their own; spans past K read scales of zero and add
+// exactly zero, so both halves run the same number of stages and barriers.
+// The halves exchange two blocks each through LDS at the end and finish one
+// weight block row each (first half's sum plus second half's).  For tile
+// counts of at most a few times 256, where a lone four-wave workgroup leaves
+// half of a CU's issue slots empty.
+template <int RANK, bool PARTIALS, int GS, int KSPLIT>
+__global__ __launch_bounds__(NT * KSPLIT, WG_PER_CU) void asp_gemm_kernel(
     const uint8_t* __restrict__ xq, const float* __restrict__ xs, const uint16_t* __restrict__ t,
     const uint8_t* __restrict__ wq, const uint32_t* __restrict__ wsp, const uint16_t* __restrict__ L2t,
     const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, int32_t* __restrict__ P, int M,
@@ -145,21 +153,26 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
   constexpr int NS = kGroup / GS;                               // scale groups per 64-channel span
   constexpr int GPS = KC * NS;                                  // scale groups per stage
   typedef StageRef<GPS> Stage;
-  __shared__ __attribute__((aligned(16))) uint8_t lds_a0[BM * ROWB], lds_b0[BN * ROWB];
-  __shared__ __attribute__((aligned(16))) uint8_t lds_a1[BM * ROWB], lds_b1[BN * ROWB];
-  __shared__ __attribute__((aligned(16))) float lds_sx0[GPS][BM], lds_sx1[GPS][BM];
-  __shared__ __attribute__((aligned(16))) uint32_t lds_sw0[GPS][BN], lds_sw1[GPS][BN];
-  const Stage st0{lds_a0, lds_b0, lds_sx0, lds_sw0};
-  const Stage st1{lds_a1, lds_b1, lds_sx1, lds_sw1};
+  static_assert(KSPLIT == 1 || (KSPLIT == 2 && !PARTIALS), "the partials are written by the unsplit kernel");
+  __shared__ __attribute__((aligned(16))) uint8_t lds_a0[KSPLIT][BM * ROWB], lds_b0[KSPLIT][BN * ROWB];
+  __shared__ __attribute__((aligned(16))) uint8_t lds_a1[KSPLIT][BM * ROWB], lds_b1[KSPLIT][BN * ROWB];
+  __shared__ __attribute__((aligned(16))) float lds_sx0[KSPLIT][GPS][BM], lds_sx1[KSPLIT][GPS][BM];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_sw0[KSPLIT][GPS][BN], lds_sw1[KSPLIT][GPS][BN];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (SGPR)
+  const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (SGPR)
+  const int kh = KSPLIT == 1 ? 0 : wave_wg >> 2;                  // half of K
+  const int wave = KSPLIT == 1 ? wave_wg : wave_wg & 3;
+  const Stage st0{lds_a0[kh], lds_b0[kh], lds_sx0[kh], lds_sw0[kh]};
+  const Stage st1{lds_a1[kh], lds_b1[kh], lds_sx1[kh], lds_sw1[kh]};
   const int wm = wave >> 1, wn = wave & 1;                      // 2 x 2 waves
-  const int G = K / kGroup;                                     // 64-channel spans
   const int GSC = K / GS;                                       // scale groups
   const int KB = K / 2;
-  const int S = (G + KC - 1) / KC;                              // ring stages
+  // 64-channel spans (with KSPLIT, of one half: whole stages) and ring stages
+  const int G = KSPLIT == 1 ? K / kGroup : ((K / kGroup + KC - 1) / KC + 1) / 2 * KC;
+  const int S = (G + KC - 1) / KC;
+  const int s_base = kh * S;                                    // first stage of this half
   const int S_full = G / KC;                                    // stages with KC groups
 
   const int tiles_m = (M + BM - 1) / BM;
@@ -198,6 +211,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
   }
 
   auto issue = [&](int s, const Stage& st) __attribute__((always_inline)) {
+    if (KSPLIT == 2) s += s_base;
     const uint32_t ko = static_cast<uint32_t>(s) * ROWB;
 #pragma unroll
     for (int i = 0; i < 4; ++i) buf_load16_lds(a_rsrc, d_off[i] + ko, st.a + (4 * wave + i) * 1024);
@@ -361,14 +375,15 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
     const buf_rsrc l_rsrc = make_rsrc(L2t + static_cast<int64_t>(n0) * RANK,
                                       static_cast<uint32_t>(min(BN, N - n0)) * RB2);
     // 128 rows of RB2 bytes = RANK / 16 kilobyte pieces per wave and array
+    // (KSPLIT: by and for the first half)
 #pragma unroll
-    for (int c = 0; c < RANK / 16; ++c) {
+    for (int c = 0; c < (kh == 0 ? RANK / 16 : 0); ++c) {
       const int piece = wave * (RANK / 16) + c;   // kilobyte of the array
       const uint32_t src = static_cast<uint32_t>(piece * 1024 + lane * 16);
       buf_load16_lds(t_rsrc, src, st1.a + piece * 1024);
       buf_load16_lds(l_rsrc, src, st1.b + piece * 1024);
     }
-    if (wave == 0) {
+    if (wave_wg == 0) {
       const buf_rsrc b_rsrc = make_rsrc(bias != nullptr ? bias + n0 : nullptr,
                                         bias != nullptr ? static_cast<uint32_t>(min(BN, N - n0)) * 2u : 0u);
       buf_load4_lds(b_rsrc, static_cast<uint32_t>(lane * 4), &st1.sx[0][0]);
@@ -382,6 +397,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
+        if (kh != 0) break;
         v16f c;
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
@@ -582,6 +598,32 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
   wait_vmcnt<0>();
   if (PARTIALS) return;
 
+  if constexpr (KSPLIT == 2) {
+    // half h finishes weight block row i = h: it puts the other row's blocks
+    // into its own first stage's code arrays (one per token block j), where all
+    // reads have ended, and takes its own row's from the other half's
+    auto part = [&](int h, int j) __attribute__((always_inline)) {
+      uint8_t* base = j == 0 ? lds_a0[h] : lds_b0[h];
+      return reinterpret_cast<float*>(base) + wave * 1024 + lane;
+    };
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float* p = part(kh, j);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) p[v * 64] = kh == 0 ? accf[1][j][v] : accf[0][j][v];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float* p = part(1 - kh, j);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float o = p[v * 64];
+        accf[0][j][v] = kh == 0 ? accf[0][j][v] + o : o + accf[1][j][v];
+      }
+    }
+  }
   // ---- epilogue: round to bf16 and store straight from registers.  Lane l
   // holds, per block (i, j), output row m = m0 + 64 wm + 32 j + l%32 and
   // columns 8 q + 4 (l/32) .. +3 (q = v/4) of the block: two bf16 pairs per
@@ -590,9 +632,10 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
   // block (p = 0, 1), so every lane stores 16 contiguous bytes and no LDS or
   // barrier is involved. ----
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int ib = 0; ib < 2 / KSPLIT; ++ib)      // (KSPLIT: the half's row, in accf[0])
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      const int i = KSPLIT == 1 ? ib : kh;
       const int m = m0 + wm * 64 + j * 32 + frow;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
@@ -603,7 +646,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             const int v = 4 * (2 * p + qq) + 2 * e;
-            w[qq][e] = bf16_pair(accf[i][j][v], accf[i][j][v + 1]);
+            w[qq][e] = bf16_pair(accf[ib][j][v], accf[ib][j][v + 1]);
           }
         // the upper half-wave's words of q = 2p trade places with the lower
         // half-wave's words of q = 2p + 1
@@ -622,27 +665,25 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void asp_gemm_kernel(
 
 static int gemm_tiles(int M, int N) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
-template <int GS>
+template <int GS, int KSPLIT>
 static hipError_t launch_asp_gemm_gs(int M, int N, int K, int r, const uint8_t* xq, const float* xs,
                                      const uint16_t* t, const uint8_t* wq, const uint32_t* wsp,
                                      const uint16_t* L2t, const uint16_t* bias, uint16_t* y, hipStream_t stream) {
-  const dim3 grid(gemm_tiles(M, N)), block(NT);
+  const dim3 grid(gemm_tiles(M, N)), block(NT * KSPLIT);
+#define QWAM_GEMM_CASE(R)                                                                                           \
+  case R:                                                                                                           \
+    hipLaunchKernelGGL((asp_gemm_kernel<R, false, GS, KSPLIT>), grid, block, 0, stream, xq, xs, t, wq, wsp, L2t,    \
+                       bias, y, nullptr, M, N, K);                                                                  \
+    break;
   switch (r) {
-    case 16:
-      hipLaunchKernelGGL((asp_gemm_kernel<16, false, GS>), grid, block, 0, stream, xq, xs, t, wq, wsp, L2t, bias, y, nullptr, M, N, K);
-      break;
-    case 32:
-      hipLaunchKernelGGL((asp_gemm_kernel<32, false, GS>), grid, block, 0, stream, xq, xs, t, wq, wsp, L2t, bias, y, nullptr, M, N, K);
-      break;
-    case 48:
-      hipLaunchKernelGGL((asp_gemm_kernel<48, false, GS>), grid, block, 0, stream, xq, xs, t, wq, wsp, L2t, bias, y, nullptr, M, N, K);
-      break;
-    case 64:
-      hipLaunchKernelGGL((asp_gemm_kernel<64, false, GS>), grid, block, 0, stream, xq, xs, t, wq, wsp, L2t, bias, y, nullptr, M, N, K);
-      break;
+    QWAM_GEMM_CASE(16)
+    QWAM_GEMM_CASE(32)
+    QWAM_GEMM_CASE(48)
+    QWAM_GEMM_CASE(64)
     default:
       return hipErrorInvalidValue;
   }
+#undef QWAM_GEMM_CASE
   return hipGetLastError();
 }
 
@@ -650,13 +691,15 @@ static hipError_t launch_asp_gemm_gs(int M, int N, int K, int r, const uint8_t* 
 // workgroups fit two to a CU runs in rounds of 512 tiles; a last round of at
 // most 256 leaves each CU one tile and is shorter.  Each round costs a start-up
 // and a part in proportion to K; the constants (in ns and ns per 1024
-// channels) are a least-squares fit, mean error 3-5%, of all forms timed at
-// 266 shapes (M = 65 .. 2048, K = 576 .. 14336, N = 1024 .. 9216, both group
-// sizes), where this rule's choice is on average 0.3% and at most 8% slower
-// than the fastest form.  Both sides at group 64, large tiles / choice:
-// M = 100, K = N = 3072 18.9 / 6.2 us; M = 415, K = 14336, N = 3072
-// 75.7 / 35.7 us; M = 512, K = 576, N = 3072 8.0 / 6.9 us; M = 333, K = 3072,
-// N = 9216 23.1 (kept) / 25.1 us; M = 4096 always the large tiles.
+// channels) are least-squares fits, mean error 3-5%, of all forms timed at
+// several hundred shapes (M = 65 .. 3000, K = 576 .. 14336, N = 1024 .. 9216,
+// both group sizes).  Large tiles / choice at group 64: M = 100, K = N = 3072
+// 18.9 / 6.2 us; M = 415, K = 14336, N = 3072 75.7 / 35.7 us; M = 512, K = 576,
+// N = 3072 8.1 / 6.9 us; M = 333, K = 3072, N = 9216 22.2 / 20.6 us (K split in
+// the large tile); M = 4096 always the large tiles.  The large tiles keep
+// calls within 3% of their estimate, and within 8% once they have more tiles
+// than CUs: there the small tiles' extra traffic showed up to 20% above
+// their estimate (M = 2048, K = 7168, N = 3072: 64 / 77 us, estimated 63 / 61).
 struct FormCost {
   int start, round, round_k, last, last_k;   // last, last_k: a last round of at most 256 tiles
 };
@@ -670,19 +713,23 @@ static int64_t form_ns(const FormCost& c, int64_t tiles, int per_cu, int K) {
   return ns;
 }
 
-static MidForm gemm_form(int M, int N, int K, int group) {
-  // large tiles; 32 x 64 by eight waves; 32 x 64 by four; 64 x 64 by four
-  static const FormCost cost[2][4] = {
-      {{2160, 5320, 8000, 2740, 5070}, {1930, 2370, 860, 0, 0}, {2660, 1960, 1500, 1240, 1030}, {2580, 2800, 2360, 1780, 1560}},
-      {{2670, 7230, 13090, 3170, 10500}, {1890, 2520, 1300, 0, 0}, {2980, 1910, 2280, 970, 1420}, {3030, 3210, 3960, 1850, 2750}}};
+static GemmForm gemm_form(int M, int N, int K, int group) {
+  // in the order of GemmForm
+  static const FormCost cost[2][5] = {
+      {{2160, 5320, 8000, 3700, 5030}, {900, 5900, 4040, 0, 0}, {1930, 2370, 860, 0, 0}, {2660, 1960, 1500, 1240, 1030},
+       {2580, 2800, 2360, 1780, 1560}},
+      {{2670, 7230, 13090, 3170, 10500}, {1800, 5350, 7150, 0, 0}, {1890, 2520, 1300, 0, 0}, {2980, 1910, 2280, 970, 1420},
+       {3030, 3210, 3960, 1850, 2750}}};
   const FormCost* c = cost[group == 32 ? 1 : 0];
   const auto tiles = [&](int tm, int tn) { return static_cast<int64_t>((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-  const int64_t ns[4] = {form_ns(c[0], tiles(BM, BN), 2, K), form_ns(c[1], tiles(32, 64), 1, K),
-                         form_ns(c[2], tiles(32, 64), 2, K), form_ns(c[3], tiles(64, 64), 2, K)};
+  const int64_t large = tiles(BM, BN);
+  const int64_t ns[5] = {form_ns(c[0], large, 2, K), form_ns(c[1], large, 1, K), form_ns(c[2], tiles(32, 64), 1, K),
+                         form_ns(c[3], tiles(32, 64), 2, K), form_ns(c[4], tiles(64, 64), 2, K)};
+  const int64_t keep = ns[0] - ns[0] / (large > 256 ? 12 : 32);
   int best = 0;
-  for (int i = 1; i < 4; ++i)
-    if (ns[i] < (best == 0 ? ns[0] - ns[0] / 32 : ns[best])) best = i;   // within 3%: the large tiles
-  return static_cast<MidForm>(best);
+  for (int i = K >= 1024 ? 1 : 2; i < 5; ++i)   // (two halves of a shorter K are all start-up)
+    if (ns[i] < (best == 0 ? keep : ns[best])) best = i;
+  return static_cast<GemmForm>(best);
 }
 
 // few tokens: the float32 scales (asp_gemm_small_kernel); otherwise the
@@ -692,21 +739,24 @@ hipError_t launch_asp_gemm(int M, int N, int K, int r, int group, const uint8_t*
                            const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                            hipStream_t stream) {
   if (M <= kSmallM) return launch_asp_gemm_small(M, N, K, r, group, xq, xs, t, wq, ws, L2t, bias, y, stream);
-  const MidForm form = gemm_form(M, N, K, group);
-  if (form != MidForm::kNone)
+  const GemmForm form = gemm_form(M, N, K, group);
+  if (form != GemmForm::kLarge && form != GemmForm::kLargeSplit)
     return launch_asp_gemm_mid(form, M, N, K, r, group, xq, xs, t, wq, wsp, L2t, bias, y, stream);
-  return group == 32 ? launch_asp_gemm_gs<32>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream)
-                     : launch_asp_gemm_gs<64>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream);
+  if (form == GemmForm::kLargeSplit)
+    return group == 32 ? launch_asp_gemm_gs<32, 2>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream)
+                       : launch_asp_gemm_gs<64, 2>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream);
+  return group == 32 ? launch_asp_gemm_gs<32, 1>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream)
+                     : launch_asp_gemm_gs<64, 1>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream);
 }
 
 hipError_t launch_group_partials(int M, int N, int K, int group, const uint8_t* xq, const uint8_t* wq,
                                  int32_t* P, hipStream_t stream) {
   if (M <= kSmallM) return launch_group_partials_small(M, N, K, group, xq, wq, P, stream);
   if (group == 32)
-    hipLaunchKernelGGL((asp_gemm_kernel<32, true, 32>), dim3(gemm_tiles(M, N)), dim3(NT), 0, stream, xq, nullptr,
+    hipLaunchKernelGGL((asp_gemm_kernel<32, true, 32, 1>), dim3(gemm_tiles(M, N)), dim3(NT), 0, stream, xq, nullptr,
                        nullptr, wq, nullptr, nullptr, nullptr, nullptr, P, M, N, K);
   else
-    hipLaunchKernelGGL((asp_gemm_kernel<32, true, 64>), dim3(gemm_tiles(M, N)), dim3(NT), 0, stream, xq, nullptr,
+    hipLaunchKernelGGL((asp_gemm_kernel<32, true, 64, 1>), dim3(gemm_tiles(M, N)), dim3(NT), 0, stream, xq, nullptr,
                        nullptr, wq, nullptr, nullptr, nullptr, nullptr, P, M, N, K);
   return hipGetLastError();
 }

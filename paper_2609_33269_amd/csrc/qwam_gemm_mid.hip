@@ -324,16 +324,16 @@ static hipError_t launch_mid(int M, int N, int K, int r, const uint8_t* xq, cons
   return hipGetLastError();
 }
 
-hipError_t launch_asp_gemm_mid(MidForm form, int M, int N, int K, int r, int group, const uint8_t* xq,
+hipError_t launch_asp_gemm_mid(GemmForm form, int M, int N, int K, int r, int group, const uint8_t* xq,
                                const float* xs, const uint16_t* t, const uint8_t* wq, const uint32_t* wsp,
                                const uint16_t* L2t, const uint16_t* bias, uint16_t* y, hipStream_t stream) {
 #define QWAM_MID_FORM(TB, MW)                                                                                 \
   return group == 32 ? launch_mid<32, TB, MW>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream)           \
                      : launch_mid<64, TB, MW>(M, N, K, r, xq, xs, t, wq, wsp, L2t, bias, y, stream);
   switch (form) {
-    case MidForm::k32x64Waves8: QWAM_MID_FORM(1, 8)
-    case MidForm::k32x64Waves4: QWAM_MID_FORM(1, 4)
-    case MidForm::k64x64Waves4: QWAM_MID_FORM(2, 4)
+    case GemmForm::k32x64Waves8: QWAM_MID_FORM(1, 8)
+    case GemmForm::k32x64Waves4: QWAM_MID_FORM(1, 4)
+    case GemmForm::k64x64Waves4: QWAM_MID_FORM(2, 4)
     default: return hipErrorInvalidValue;
   }
 #undef QWAM_MID_FORM

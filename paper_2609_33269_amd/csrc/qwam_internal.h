@@ -76,10 +76,12 @@ hipError_t launch_asp_gemm_small(int M, int N, int K, int r, int group, const ui
                                  const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                                  hipStream_t stream);
 
-// the GEMM in tiles of 32 or 64 tokens x 64 channels with K split over the
-// workgroup's waves, for a few hundred tokens
-enum class MidForm { kNone = 0, k32x64Waves8 = 1, k32x64Waves4 = 2, k64x64Waves4 = 3 };
-hipError_t launch_asp_gemm_mid(MidForm form, int M, int N, int K, int r, int group, const uint8_t* xq,
+// Forms of the GEMM for more than kSmallM tokens: 128 x 128 tiles by four
+// waves, the same by eight with K in two halves, and tiles of 32 or 64 tokens
+// x 64 channels with K split over the workgroup's waves (for a few hundred
+// tokens)
+enum class GemmForm { kLarge = 0, kLargeSplit = 1, k32x64Waves8 = 2, k32x64Waves4 = 3, k64x64Waves4 = 4 };
+hipError_t launch_asp_gemm_mid(GemmForm form, int M, int N, int K, int r, int group, const uint8_t* xq,
                                const float* xs, const uint16_t* t, const uint8_t* wq, const uint32_t* wsp,
                                const uint16_t* L2t, const uint16_t* bias, uint16_t* y, hipStream_t stream);
 
