@@ -16,9 +16,9 @@
 //     A is d x d and read once per product (HBM-bound); the block is p x d
 //     and stays in L2;
 //   * orthonormalisation by CholeskyQR: Gram matrix in float64 (per-chunk
-//     partials, then a fixed-order sum in a kernel of its own), Cholesky and
-//     triangular inverse by blocks of 16 rows in one workgroup, then
-//     V = W R^-1 (tiled, float64 sums); one pass per iteration, two (i.e.
+//     partials, then a fixed-order sum in a kernel of its own), Cholesky by
+//     blocks of 16 rows in one workgroup, then V = W R^-1 by block
+//     substitution (float64); one pass per iteration, two (i.e.
 //     CholeskyQR2) on the block that enters Rayleigh-Ritz;
 //   * Rayleigh-Ritz: T = V^T G~ V (p x p, float64), parallel cyclic Jacobi in
 //     one workgroup (disjoint rotation pairs by the circle method), Ritz
@@ -324,10 +324,11 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
   return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-// C = R^T R (Cholesky, R upper) and Rinv = R^-1 (upper, its lower part exact
-// zeros) to global memory, in one workgroup of four waves.  Lane j holds
-// column j; wave q holds rows 16 q .. 16 q + 15 of it in registers (blocks of
-// 16 rows).  Only the upper triangle of C is read.
+// C = R^T R (Cholesky, R upper), in one workgroup of four waves: out holds the
+// rows of R above the 16 x 16 diagonal blocks, and the inverses of those
+// blocks in their place (zeros below the diagonal).  Lane j holds column j;
+// wave q holds rows 16 q .. 16 q + 15 of it in registers.  Only the upper
+// triangle of C is read.
 //   * Factorisation, right-looking by blocks: the wave that owns diagonal
 //     block b factors its 16 rows alone (step k: the pivot from lane k, lane
 //     j forms R[k][j], the row goes to LDS and the wave updates its remaining
@@ -336,23 +337,20 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
 //   * A pivot below 1e-13 of the largest diagonal entry (a block of lower
 //     rank) is raised to that floor, so the inverse stays finite; the next
 //     iterations refill such a direction.
-//   * Inverse, R z = e_j for column j, by blocks from the last: the owner wave
-//     solves its 16 rows (column-oriented within the block), its rows of z go
-//     to LDS, one barrier, and every wave above the block subtracts the
-//     block's contribution from its rows.
+//   * A wave inverts its diagonal block right after it has factored it, while
+//     the others go on (the whole inverse was a second chain over the blocks,
+//     10 of this kernel's 23 us; the basis update does that substitution).
 // Inside a block the row of R reaches the wave's other lanes by cross-lane
 // reads (no LDS round trip on the chain of pivots).
 constexpr int CB = 16;          // rows per block (and per wave)
 
-__global__ __launch_bounds__(NT) void eig_chol_kernel(const double* __restrict__ C, double* __restrict__ Rinv) {
+__global__ __launch_bounds__(NT) void eig_chol_kernel(const double* __restrict__ C, double* __restrict__ Rout) {
   __shared__ __attribute__((aligned(16))) double rl[P][P + 2];    // rows of R
   __shared__ __attribute__((aligned(16))) double rc[P][P + 2];    // columns of R: rc[j][k] = R[k][j]
-  __shared__ __attribute__((aligned(16))) double zl[P][P + 2];    // rows of R^-1 as they are solved
-  __shared__ double dinv[P];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r0 = CB * wave;
-  double c[CB];
+  double c[CB], dinv[CB];
 #pragma unroll
   for (int i = 0; i < CB; ++i) c[i] = C[(r0 + i) * P + lane];
   double m = C[lane * (P + 1)];
@@ -377,7 +375,7 @@ __global__ __launch_bounds__(NT) void eig_chol_kernel(const double* __restrict__
         c[kk] = rk;
         rl[k][lane] = rk;
         rc[lane][k] = rk;
-        if (lane == 0) dinv[k] = inv;
+        dinv[kk] = inv;
         // R[k][i] of the block's later rows i from lane i (the next pivot's
         // row first)
 #pragma unroll
@@ -396,92 +394,130 @@ __global__ __launch_bounds__(NT) void eig_chol_kernel(const double* __restrict__
     }
   }
 
+  // R_bb z = e_j for column j of the wave's own diagonal block (lane 16 q + j),
+  // column-oriented from the last row; other lanes solve for zero
   double z[CB];
 #pragma unroll
   for (int i = 0; i < CB; ++i) z[i] = (r0 + i == lane) ? 1.0 : 0.0;
 #pragma unroll
-  for (int b = P / CB - 1; b >= 0; --b) {
-    if (wave == b) {
+  for (int ii = CB - 1; ii >= 0; --ii) {
+    z[ii] *= dinv[ii];
 #pragma unroll
-      for (int ii = CB - 1; ii >= 0; --ii) {
-        const int i = CB * b + ii;
-        z[ii] *= dinv[i];
-        zl[i][lane] = z[ii];
-#pragma unroll
-        for (int kk = 0; kk < ii; ++kk) z[kk] = __builtin_fma(-rc[i][CB * b + kk], z[ii], z[kk]);
-      }
-    }
-    __syncthreads();
-    if (wave < b) {
-#pragma unroll
-      for (int ii = 0; ii < CB; ++ii) {
-        const int i = CB * b + ii;
-        const double zi = zl[i][lane];
-#pragma unroll
-        for (int kk = 0; kk < CB; ++kk) z[kk] = __builtin_fma(-rc[i][r0 + kk], zi, z[kk]);
-      }
-    }
+    for (int kk = 0; kk < ii; ++kk) z[kk] = __builtin_fma(-rc[r0 + ii][r0 + kk], z[ii], z[kk]);
   }
+  const bool own = (lane >> 4) == wave;
 #pragma unroll
-  for (int i = 0; i < CB; ++i) Rinv[(r0 + i) * P + lane] = z[i];
+  for (int i = 0; i < CB; ++i) Rout[(r0 + i) * P + lane] = own ? z[i] : c[i];
 }
 
-// Vt[i][n] = sum over k of Rinv[k][i] Wt[k][n] (V = W R^-1; Rinv is zero below
-// its diagonal), k ascending, float64, for the AT columns n of the workgroup.
-// Thread (ti, tn) = (tid / 16, tid % 16) owns rows 4 ti .. 4 ti + 3 and columns
-// 2 tn, 2 tn + 1.
-__global__ __launch_bounds__(NT) void eig_apply_kernel(const float* __restrict__ Wt, const double* __restrict__ Rinv,
+// V = W R^-1 by blocks of 16 rows (Rf: eig_chol_kernel's output): for block b,
+// V_b = Rinv_bb^T (W_b - sum over b' < b of R_b'b^T V_b'), float64, for the AT
+// columns n of the workgroup, every sum in ascending order.  Thread
+// (ti, tn) = (tid / 16, tid % 16) owns row ti of each block and columns 2 tn,
+// 2 tn + 1.
+__global__ __launch_bounds__(NT) void eig_apply_kernel(const float* __restrict__ Wt, const double* __restrict__ Rf,
                                                        float* __restrict__ Vt, int d) {
   __shared__ __attribute__((aligned(16))) double rs[P][P];
-  __shared__ __attribute__((aligned(16))) double wsd[P][AT + 2];
+  __shared__ __attribute__((aligned(16))) double vs[P][AT + 2];     // W, then V block by block
+  __shared__ __attribute__((aligned(16))) double us[CB][AT + 2];    // a block's right-hand side
   const int tid = threadIdx.x;
   const int n0 = blockIdx.x * AT;
   for (int e = tid; e < P * P / 2; e += NT)
-    *reinterpret_cast<double2*>(&rs[0][2 * e]) = reinterpret_cast<const double2*>(Rinv)[e];
+    *reinterpret_cast<double2*>(&rs[0][2 * e]) = reinterpret_cast<const double2*>(Rf)[e];
   for (int e = tid; e < P * AT / 4; e += NT) {
     const int k = e / (AT / 4), c4 = e % (AT / 4);
     const float4 w = *reinterpret_cast<const float4*>(Wt + static_cast<int64_t>(k) * d + n0 + 4 * c4);
-    *reinterpret_cast<double2*>(&wsd[k][4 * c4]) = make_double2(w.x, w.y);
-    *reinterpret_cast<double2*>(&wsd[k][4 * c4 + 2]) = make_double2(w.z, w.w);
+    *reinterpret_cast<double2*>(&vs[k][4 * c4]) = make_double2(w.x, w.y);
+    *reinterpret_cast<double2*>(&vs[k][4 * c4 + 2]) = make_double2(w.z, w.w);
   }
   __syncthreads();
   const int ti = tid >> 4, tn = tid & 15;
-  double acc[4][2];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) acc[p][0] = acc[p][1] = 0.0;
+  for (int b = 0; b < P / CB; ++b) {
+    const int row = CB * b + ti;
+    double2 u = *reinterpret_cast<const double2*>(&vs[row][2 * tn]);
 #pragma unroll 8
-  for (int k = 0; k < P; ++k) {
-    const double2 r01 = *reinterpret_cast<const double2*>(&rs[k][4 * ti]);
-    const double2 r23 = *reinterpret_cast<const double2*>(&rs[k][4 * ti + 2]);
-    const double2 w = *reinterpret_cast<const double2*>(&wsd[k][2 * tn]);
-    const double r[4] = {r01.x, r01.y, r23.x, r23.y};
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      acc[p][0] = __builtin_fma(r[p], w.x, acc[p][0]);
-      acc[p][1] = __builtin_fma(r[p], w.y, acc[p][1]);
+    for (int k = 0; k < CB * b; ++k) {
+      const double r = rs[k][row];
+      const double2 v = *reinterpret_cast<const double2*>(&vs[k][2 * tn]);
+      u.x = __builtin_fma(-r, v.x, u.x);
+      u.y = __builtin_fma(-r, v.y, u.y);
     }
+    *reinterpret_cast<double2*>(&us[ti][2 * tn]) = u;
+    __syncthreads();
+    double2 v = make_double2(0.0, 0.0);
+#pragma unroll 8
+    for (int k = 0; k < CB; ++k) {
+      const double r = rs[CB * b + k][row];            // zero below the diagonal
+      const double2 w = *reinterpret_cast<const double2*>(&us[k][2 * tn]);
+      v.x = __builtin_fma(r, w.x, v.x);
+      v.y = __builtin_fma(r, w.y, v.y);
+    }
+    *reinterpret_cast<double2*>(&vs[row][2 * tn]) = v;
+    *reinterpret_cast<float2*>(Vt + static_cast<int64_t>(row) * d + n0 + 2 * tn) =
+        make_float2(static_cast<float>(v.x), static_cast<float>(v.y));
+    __syncthreads();
   }
-#pragma unroll
-  for (int p = 0; p < 4; ++p)
-    *reinterpret_cast<float2*>(Vt + static_cast<int64_t>(4 * ti + p) * d + n0 + 2 * tn) =
-        make_float2(static_cast<float>(acc[p][0]), static_cast<float>(acc[p][1]));
+}
+
+// Rotation (c, s) that zeroes T_ab of a symmetric 2 x 2 block (the smaller
+// angle), with diff = T_bb - T_aa: with h = sqrt((diff/2)^2 + T_ab^2),
+// c^2 = (1 + |diff| / (2 h)) / 2 and s = sign(diff) T_ab / (2 h c).  Two
+// reciprocal square roots on the chain (the form over tau and tan takes two
+// more reciprocals).  Squares that would leave the range of a double take that
+// form, Golub and Van Loan's symmetric 2 x 2 Schur step.
+__device__ __forceinline__ void jacobi_rotation(double diff, double apq, double& c, double& s) {
+  c = 1.0;
+  s = 0.0;
+  if (apq == 0.0) return;
+  const double d = 0.5 * diff;
+  const double h2 = __builtin_fma(d, d, apq * apq);
+  if (h2 > 1e-280 && h2 < 1e280) {
+    const double r = rsqrt_f64(h2);                      // 1 / h
+    const double c2 = __builtin_fma(0.5 * __builtin_fabs(d), r, 0.5);
+    const double ic = rsqrt_f64(c2);                     // 1 / c, c2 in [0.5, 1]
+    c = c2 * ic;
+    s = (d >= 0.0 ? 0.5 : -0.5) * apq * r * ic;
+    return;
+  }
+  const double aa = __builtin_fabs(apq);
+  double tt;
+  if (__builtin_fabs(diff) > 1e100 * aa) {
+    tt = 0.5 * apq / diff;
+  } else {
+    // tau = diff / (2 T_ab); tt = sign(tau) / (|tau| + sqrt(1 + tau^2))
+    const double tau = diff * rcp_f64(2.0 * apq);
+    const double q = 1.0 + tau * tau;
+    const double root = q * rsqrt_f64(q);
+    tt = (tau >= 0.0 ? 1.0 : -1.0) * rcp_f64(__builtin_fabs(tau) + root);
+  }
+  c = rsqrt_f64(1.0 + tt * tt);
+  s = tt * c;
 }
 
 // One workgroup: T = the summed V^T (G~ V), symmetrised; cyclic Jacobi with
 // the 32 disjoint pairs of each round of the circle method (index 0 fixed,
 // 1 .. 63 rotating), a sweep being 63 rounds; the rotation of each pair zeroes
-// T[a][b] (Golub and Van Loan's symmetric 2 x 2 Schur step).  The pairs of a
-// round are disjoint and cover every index, so T <- J^T T J splits into the
-// 32 x 32 independent 2 x 2 blocks (rows of pair k, columns of pair m), each
-// updated in one pass (rows, then columns), and Q <- Q J into 64 x 32
-// independent row pairs.  Stops when the off-diagonal mass is below 1e-26 of
-// the diagonal's, or after 30 sweeps.  Out: theta (eigenvalues, descending),
-// Q (its columns the eigenvectors of T in that order), both float64.
+// T[a][b].  The pairs of a round are disjoint and cover every index, so
+// T <- J^T T J splits into independent 2 x 2 blocks (rows of pair k, columns of
+// pair m), and Q <- Q J into 64 x 32 independent row pairs.
+//   * T is symmetric: only its upper triangle is kept up to date, i.e. the 496
+//     blocks k < m (one thread each) and the 32 diagonal ones, which the
+//     threads that formed the rotations write.
+//   * A round is two steps with a barrier each: T's blocks; then the next
+//     round's rotations (wave 0) beside Q's update (the other waves).
+// Four sweeps at p = 64: 301 -> 236 us against both triangles of T and Q in one
+// step after the rotations.  Double-precision instructions, not LDS traffic,
+// are what a round waits for: every thread forming its own two rotations (one
+// barrier a round, Q in registers after each sweep) took 396 us.
+// Stops when the off-diagonal mass is below 1e-26 of the diagonal's, or after
+// 30 sweeps.  Out: theta (eigenvalues, descending), Q (its columns the
+// eigenvectors of T in that order), both float64.
 __global__ __launch_bounds__(JT) void eig_jacobi_kernel(const double* __restrict__ C, double* __restrict__ Qout,
                                                         double* __restrict__ theta) {
   __shared__ double t[P][P + 1], q[P][P + 1];
-  __shared__ double2 rot[P / 2];
-  __shared__ int2 prs[P / 2];
+  __shared__ double2 rot[2][P / 2];
+  __shared__ int2 prs[2][P / 2];
   __shared__ double red[2][JT];
   __shared__ int order[P];
   __shared__ int done;
@@ -492,13 +528,43 @@ __global__ __launch_bounds__(JT) void eig_jacobi_kernel(const double* __restrict
     q[a][b] = a == b ? 1.0 : 0.0;
   }
   __syncthreads();
-  const int bk = tid >> 4, bm0 = tid & 15;     // T blocks (bk, bm0 + 16 j)
-  const int qm = tid & 31, qi0 = tid >> 5;     // Q rows qi0 + 16 u of pair qm
+  // T block (bk, bm), bk < bm, of this thread: thread e of the 496 in row order
+  int bk = 0, bm = 0;
+  {
+    int e = tid;
+    while (bk < P / 2 - 1 && e >= P / 2 - 1 - bk) {
+      e -= P / 2 - 1 - bk;
+      ++bk;
+    }
+    bm = bk + 1 + e;
+  }
+  const bool has_block = tid < (P / 2) * (P / 2 - 1) / 2;
+  // T[i][j] where it is kept
+  auto at = [&](int i, int j) __attribute__((always_inline)) -> double& { return i < j ? t[i][j] : t[j][i]; };
+  // rotation of pair tid of a round, and the pair's new diagonal entries
+  double new_aa = 0.0, new_bb = 0.0;
+  auto rotation = [&](int round, int buf) __attribute__((always_inline)) {
+    const int k = tid;
+    const int pa = (k == 0) ? 0 : ((k - 1 + round) % (P - 1)) + 1;
+    const int pb = ((P - 1 - k - 1 + round) % (P - 1)) + 1;
+    const int a = pa < pb ? pa : pb, b = pa < pb ? pb : pa;
+    const double taa = t[a][a], tbb = t[b][b], tab = t[a][b];
+    double c, s;
+    jacobi_rotation(tbb - taa, tab, c, s);
+    // c^2 aa - 2 c s ab + s^2 bb and its counterpart, as aa - tan ab and bb + tan ab
+    const double shift = s * rcp_f64(c) * tab;
+    new_aa = taa - shift;
+    new_bb = tbb + shift;
+    prs[buf][k] = make_int2(a, b);
+    rot[buf][k] = make_double2(c, s);
+  };
   for (int sweep = 0; sweep < 30; ++sweep) {
     double off = 0.0, dia = 0.0;
     for (int e = tid; e < P * P; e += JT) {
-      const double v = t[e / P][e % P];
-      if (e / P == e % P) dia += v * v; else off += v * v;
+      const int i = e / P, j = e % P;
+      const double v = t[i][j];
+      if (i == j) dia += v * v;
+      else if (i < j) off += 2.0 * v * v;
     }
     red[0][tid] = off;
     red[1][tid] = dia;
@@ -513,61 +579,43 @@ __global__ __launch_bounds__(JT) void eig_jacobi_kernel(const double* __restrict
     if (tid == 0) done = !(red[0][0] > 1e-26 * red[1][0]);
     __syncthreads();
     if (done) break;
+    if (tid < P / 2) rotation(0, 0);
+    __syncthreads();
     for (int round = 0; round < P - 1; ++round) {
+      const int buf = round & 1;
+      if (has_block) {
+        const int2 ab = prs[buf][bk], ef = prs[buf][bm];
+        const double2 cs = rot[buf][bk], cs2 = rot[buf][bm];
+        double &pae = at(ab.x, ef.x), &paf = at(ab.x, ef.y), &pbe = at(ab.y, ef.x), &pbf = at(ab.y, ef.y);
+        const double xae = pae, xaf = paf, xbe = pbe, xbf = pbf;
+        const double yae = cs.x * xae - cs.y * xbe, yaf = cs.x * xaf - cs.y * xbf;
+        const double ybe = cs.y * xae + cs.x * xbe, ybf = cs.y * xaf + cs.x * xbf;
+        pae = cs2.x * yae - cs2.y * yaf;
+        paf = cs2.y * yae + cs2.x * yaf;
+        pbe = cs2.x * ybe - cs2.y * ybf;
+        pbf = cs2.y * ybe + cs2.x * ybf;
+      }
       if (tid < P / 2) {
-        const int k = tid;
-        const int pa = (k == 0) ? 0 : ((k - 1 + round) % (P - 1)) + 1;
-        const int pb = ((P - 1 - k - 1 + round) % (P - 1)) + 1;
-        const int a = pa < pb ? pa : pb, b = pa < pb ? pb : pa;
-        double c = 1.0, s = 0.0;
-        const double apq = t[a][b];
-        if (apq != 0.0) {
-          // tau = (T_bb - T_aa) / (2 T_ab); tt = sign(tau) / (|tau| + sqrt(1 + tau^2)),
-          // the smaller root of tt^2 + 2 tau tt - 1 = 0; c = 1 / sqrt(1 + tt^2).
-          // Reciprocals and square roots by refined hardware estimates; a
-          // |tau| beyond 1e100 (tau^2 would overflow) takes tt = 1 / (2 tau)
-          const double diff = t[b][b] - t[a][a];
-          const double aa = __builtin_fabs(apq);
-          double tt;
-          if (__builtin_fabs(diff) > 1e100 * aa) {
-            tt = 0.5 * apq / diff;
-          } else {
-            const double tau = diff * rcp_f64(2.0 * apq);
-            const double q = 1.0 + tau * tau;
-            const double root = q * rsqrt_f64(q);
-            tt = (tau >= 0.0 ? 1.0 : -1.0) * rcp_f64(__builtin_fabs(tau) + root);
-          }
-          c = rsqrt_f64(1.0 + tt * tt);
-          s = tt * c;
-        }
-        prs[k] = make_int2(a, b);
-        rot[k] = make_double2(c, s);
+        const int2 ab = prs[buf][tid];
+        t[ab.x][ab.x] = new_aa;
+        t[ab.y][ab.y] = new_bb;
+        t[ab.x][ab.y] = 0.0;
       }
       __syncthreads();
-      {
-        const int2 ab = prs[bk];
-        const double2 cs = rot[bk];
+      if (tid < P / 2) {
+        if (round + 1 < P - 1) rotation(round + 1, buf ^ 1);
+      } else if (tid >= 64) {
+        const int qm = tid & 31;                // pair; rows (tid - 64) / 32 + 14 u
+        const int2 gh = prs[buf][qm];
+        const double2 cq = rot[buf][qm];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int bm = bm0 + 16 * j;
-          const int2 ef = prs[bm];
-          const double2 cs2 = rot[bm];
-          const double xae = t[ab.x][ef.x], xaf = t[ab.x][ef.y], xbe = t[ab.y][ef.x], xbf = t[ab.y][ef.y];
-          const double yae = cs.x * xae - cs.y * xbe, yaf = cs.x * xaf - cs.y * xbf;
-          const double ybe = cs.y * xae + cs.x * xbe, ybf = cs.y * xaf + cs.x * xbf;
-          t[ab.x][ef.x] = cs2.x * yae - cs2.y * yaf;
-          t[ab.x][ef.y] = cs2.y * yae + cs2.x * yaf;
-          t[ab.y][ef.x] = cs2.x * ybe - cs2.y * ybf;
-          t[ab.y][ef.y] = cs2.y * ybe + cs2.x * ybf;
-        }
-        const int2 gh = prs[qm];
-        const double2 cq = rot[qm];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = qi0 + 16 * u;
-          const double qa = q[i][gh.x], qb = q[i][gh.y];
-          q[i][gh.x] = cq.x * qa - cq.y * qb;
-          q[i][gh.y] = cq.y * qa + cq.x * qb;
+        for (int u = 0; u < 5; ++u) {
+          const int i = ((tid - 64) >> 5) + 14 * u;
+          if (i < P) {
+            const double qa = q[i][gh.x], qb = q[i][gh.y];
+            q[i][gh.x] = cq.x * qa - cq.y * qb;
+            q[i][gh.y] = cq.y * qa + cq.x * qb;
+          }
         }
       }
       __syncthreads();
