@@ -16,10 +16,14 @@ namespace qwam {
 
 // ---------------------------------------------------------------------------
 // Weight pack: 4 lanes per (row, 64-channel span); each lane owns 16
-// consecutive floats, i.e. one code block.  The first `inv_blocks` workgroups
-// write 1/lambda instead (a launch of its own took 4.8 us behind the pack of a
-// 14336 x 3072 layer, which itself runs at 4.7 TB/s of the 5.2 TB/s that a
-// large copy reaches: 47.0 us for both launches, 45.2 us for one).
+// consecutive floats, i.e. one code block.  A workgroup takes 16 rows x 4 spans:
+// whole lines of R and of the codes, and 16 neighbours of each scale array
+// row, whose 4-byte stores then meet in one L2 (rows of spans dealt out one
+// after another left every such line to all eight XCDs' L2s in pieces: 14336 x
+// 3072 47.9 -> 39.9 us, i.e. 5.1 of the 5.2 TB/s that a large copy reaches;
+// 9216 x 3072, group 32 38.3 -> 28.3 us).
+// The first `inv_blocks` workgroups
+// write 1/lambda instead (a launch of its own took 4.8 us behind the pack).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void pack_weights_kernel(const float* __restrict__ R,
                                                            const float* __restrict__ smooth,
@@ -33,20 +37,21 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const float* __restri
     return;
   }
   const int G = K / kGroup;
-  const int64_t team = (static_cast<int64_t>(blockIdx.x - inv_blocks) * blockDim.x + threadIdx.x) >> 2;
+  const int gtiles = (G + 3) / 4;
+  const int tile = static_cast<int>(blockIdx.x) - inv_blocks;
   const int sub = threadIdx.x & 3;
-  const bool active = team < static_cast<int64_t>(N) * G;
-  const int n = active ? static_cast<int>(team / G) : 0;
-  const int g = active ? static_cast<int>(team % G) : 0;
+  const int g = (tile % gtiles) * 4 + ((threadIdx.x >> 2) & 3);
+  const int n = (tile / gtiles) * 16 + (threadIdx.x >> 4);
+  const bool active = g < G && n < N;
 
   float v[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) v[i] = 0.0f;
   if (active) {
-    const float4* src = reinterpret_cast<const float4*>(R + static_cast<int64_t>(n) * K + g * kGroup + sub * 16);
+    const v4f* src = reinterpret_cast<const v4f*>(R + static_cast<int64_t>(n) * K + g * kGroup + sub * 16);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float4 a = src[i];
+      const v4f a = src[i];
       v[4 * i] = a.x; v[4 * i + 1] = a.y; v[4 * i + 2] = a.z; v[4 * i + 3] = a.w;
     }
   }
@@ -352,8 +357,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_deflated_
 // ---------------------------------------------------------------------------
 hipError_t launch_pack_weights(int K, int N, int group, const float* R, const float* smooth, uint8_t* wq,
                                float* ws, uint32_t* wsp, float* inv_smooth, hipStream_t stream) {
-  const int64_t teams = static_cast<int64_t>(N) * (K / kGroup);
-  const int64_t blocks = (teams * 4 + 255) / 256;
+  const int64_t blocks = static_cast<int64_t>((N + 15) / 16) * ((K / kGroup + 3) / 4);
   const int inv_blocks = (K + 255) / 256;
   hipLaunchKernelGGL(pack_weights_kernel, dim3(static_cast<unsigned>(blocks + inv_blocks)), dim3(256), 0, stream, R,
                      smooth, wq, ws, wsp, inv_smooth, N, K, group == 32 ? 1 : 0, inv_blocks);
