@@ -12,10 +12,9 @@
 //     branch t . L2 on the bf16 matrix cores, the bias, the store).  The
 //     fused few-token layer uses the same split and the same order, so both
 //     paths give the same y from the same codes, scales and t;
-//   * every operand goes straight from HBM/L2 into the MFMA register layout
-//     (lane l: row / column l % 32, half l / 32 of a group, 16 bytes = 32
-//     codes), four groups per chunk, two chunks in flight: with eight waves a
-//     K of 4096 is one memory round trip;
+//   * up to K = kDirectK every operand goes straight from HBM/L2 into the MFMA
+//     register layout (lane l: row / column l % 32, half l / 32 of a group, 16
+//     bytes = 32 codes): one memory round trip;
 //   * a longer K (STAGED) comes through LDS instead: each wave copies stages of
 //     four groups (one cache line of every row, eight lanes per line,
 //     buffer_load ... lds) into two buffers of its own, reads a stage into
