@@ -35,12 +35,13 @@ struct ActSplit {
 };
 // Split from two workgroups per block on (at most kSplitBlocks blocks), where
 // K is long enough to pay for the second launch (units of four groups; tiles
-// of the rotated kernels).  Graph replays, r = 32, unsplit / split: plain
-// K = 2048 7.4 us (kept), K = 5120 11.9 / 6.9 us, K = 14336 26.4 / 7.7 us (33
-// tokens) and 29.8 / 21.5 us (2048 tokens); deflated K = 1024 11.9 us (kept),
-// K = 5120 43.9 / 12.4 us, K = 14336 117 / 15 us; rotated K = 2048 12.8 / 9.9
-// us, K = 14336 70.6 / 11.3 us; rotated and deflated K = 2048 30.7 / 22.2 us,
-// K = 14336 214 / 24 us (33 tokens) and 218 / 120 us (2048 tokens).
+// of the rotated kernels).  Graph replays, r = 32, 33 tokens, unsplit / split:
+// plain K = 2048 7.4 us (kept), K = 5120 11.9 / 6.9 us, K = 14336 26.3 / 7.7
+// us; deflated K = 1024 11.8 us (kept), K = 2048 20.5 / 9.5 us, K = 14336 117 /
+// 14.8 us; rotated K = 2048 10.9 / 8.9 us, K = 14336 57.8 / 10.3 us; rotated and
+// deflated K = 2048 27.8 / 20.2 us, K = 14336 173 / 22.2 us.  2048 tokens (two
+// splits), K = 14336: 29.8 / 21.6, 119 / 68, 61 / 36 and 177 / 104 us.  As many
+// splits as one round of 256 workgroups holds: 384 to 768 took 10-30% longer.
 constexpr int kSplitBlocks = 128;
 constexpr int kMinUnits = 12, kMinUnitsDeflated = 6;
 constexpr int kMinTiles = 2;

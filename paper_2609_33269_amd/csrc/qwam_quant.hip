@@ -101,9 +101,9 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const float* __restri
 //
 // With few token blocks (act_split) the workgroup takes a part of K instead,
 // and its sums of t go to a workspace that split_t_kernel adds up: one
-// workgroup's reads of x and L1 (28 KB + 64 bytes of L1 per channel and 16
-// tokens) are what a call of a few tokens waits for, at about 50 B/ns per CU
-// (33 tokens, K = 14336: 26.4 us in three workgroups, 7.7 us in 168).
+// workgroup's reads of x and L1 (32 + 2 r bytes per channel) are what a call
+// of a few tokens waits for, at about 50 B/ns per CU
+// (33 tokens, K = 14336: 26.3 us in three workgroups, 7.7 us in 168).
 // ---------------------------------------------------------------------------
 template <int RANK, bool INV_LDS>
 __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
