@@ -106,3 +106,37 @@ def test_split_equals_unsplit(M, K, r, group, rotated, deflate):
     else:
         xt = O.transformed_activations(d.x, O.inverse_smoothing(f["lam"]), int(f.get("hadamard", 0)))
         check_t(bits(split[2]), O.down_projection(xt, f["L1"]), xt, f["L1"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rotated", [False, True])
+def test_split_calls_in_a_graph(rotated):
+    """Split calls (plain and deflated) and their GEMM captured with the binding's
+    workspace from the graph's pool: every replay equals the eager call, with
+    eager work that takes and drops memory between the replays, also on new
+    inputs."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    d = I.custom(35, 3072, 64, 32, seed=5, n_outliers=5)
+    layer = gpu_layer(oracle_factors(d, hadamard=rotated))
+    x = bf16_dev(d.x)
+
+    def step():
+        return [Q.forward(layer, x, deflate=f) for f in (False, True)]
+
+    step()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ys = step()
+    for i in range(4):
+        x.copy_(bf16_dev(np.roll(d.x, i, axis=0)))
+        eager = step()
+        junk = [torch.full((1 << 20,), float("nan"), device="cuda:0") for _ in range(4)]
+        for y in ys:
+            y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        del junk
+        for a, b in zip(eager, ys):
+            assert (bits(a) == bits(b)).all(), f"replay {i}"
