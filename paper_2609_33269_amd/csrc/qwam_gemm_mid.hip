@@ -227,7 +227,7 @@ __global__ __launch_bounds__(64 * MW, 8 / MW) void asp_gemm_mid_kernel(
   }
 
   // partial tiles -> the waves' own stage buffers (all copies have landed):
-  // registers r = 16 block + v, the first half of them in stage 0's
+  // registers r = 16 block + v
   auto part = [&](int w, int r) __attribute__((always_inline)) {
     return reinterpret_cast<float*>(st0[w]) + r * 64 + lane;
   };
