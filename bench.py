@@ -84,7 +84,14 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 METRIC = "ASP W4A4+r32 linear: effective TOPS & % int8 MFMA peak at 4096×3072×14336"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_asp_gemm_ffn_up.json")
 GEMM_SRCS = [os.path.join(ROOT, "paper_2609_33269_amd", "csrc", f) for f in ("qwam_gemm.hip", "qwam_device.h", "qwam_mfma.h")]
-GEMM_KERNEL = "asp_gemm_kernel<32, false, 64>"
+
+
+def gemm_kernel(group: int = GROUP) -> str:
+    """The GEMM instance of the bench's shapes: whole 128 x 128 tiles, K not split."""
+    return f"asp_gemm_kernel<{R_RANK}, false, {group}, 1>"
+
+
+GEMM_KERNEL = gemm_kernel()
 COPY_KERNEL = "(anonymous namespace)::copy_kernel("   # the streaming copy of qwam_probe_copy
 
 
@@ -873,7 +880,7 @@ def main():
                    "act": ("bf16(GELU_erf(N(0,1)))" if args.workload == "video_dit_ffn_down"
                            else "N(0,1), 1% channels x U_log(10,50)"), "weights": "N(0,1/K)",
                    "rotated_buffer_sets": nrot},
-        "roofline": {"bound": "mfma", "kernel": f"asp_gemm_kernel<{R_RANK}, false, {args.group}>",
+        "roofline": {"bound": "mfma", "kernel": gemm_kernel(args.group),
                      "achieved": round(k2_tops, 1),
                      "peak": FP6_MFMA_PEAK, "unit": "TFLOP/s", "frac": round(k2_tops / FP6_MFMA_PEAK, 4),
                      "traffic": traffic, "algorithmic_bytes": gemm_bytes},

@@ -54,3 +54,15 @@ def test_reduce_counters_requires_both_kernels(tmp_path):
     _write_counters(write, [(g, 500.0)])
     with pytest.raises(SystemExit):
         bench.reduce_counters(str(fetch), str(write), 256)
+
+
+@pytest.mark.parametrize("group", [64, 32])
+def test_kernel_names_are_those_of_the_library(group):
+    """The names that select counter rows and label the roofline are kernels the library was built with."""
+    from paper_2609_33269_amd import build, qwam
+    if not os.path.exists(qwam.LIB_PATH):
+        build.build()
+    names = subprocess.run(["nm", "-C", qwam.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    assert f" qwam::{bench.gemm_kernel(group)}(" in names
+    assert bench.COPY_KERNEL.replace("copy_kernel", "__device_stub__copy_kernel") in names
+    assert bench.GEMM_KERNEL == bench.gemm_kernel(64)
