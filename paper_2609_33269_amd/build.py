@@ -1,5 +1,7 @@
 """Build libqwam.so (HIP kernels for gfx950 + the C ABI) in-tree with hipcc, and
 the CPython module of its per-token calls (_qwam_call) with the host compiler.
+The library needs hipcc only.  The module also needs g++ and PyTorch's headers;
+when it does not build, the library is linked all the same and the error follows.
 
 Usage: python -m paper_2609_33269_amd.build [-v]
 """
@@ -8,6 +10,7 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -53,10 +56,22 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _rocm_root() -> str:
+    """The ROCm installation of HIPCC, which may be a path, a link or a name on PATH."""
+    path = shutil.which(HIPCC)
+    if path is None:
+        raise RuntimeError(f"{HIPCC}: no such program")
+    for p in (path, os.path.realpath(path)):
+        root = os.path.dirname(os.path.dirname(os.path.abspath(p)))
+        if os.path.exists(os.path.join(root, "include", "hip", "hip_runtime.h")):
+            return root
+    raise RuntimeError(f"no HIP headers beside {path}")
+
+
 def _build_call_module(verbose: bool) -> None:
     import torch
     tdir = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    rocm = _rocm_root()
     tmp = CALL_MODULE + ".tmp"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
@@ -79,7 +94,6 @@ def build(verbose: bool = False) -> str:
     with cf.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
         call = ex.submit(_build_call_module, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
-        call.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:
@@ -88,6 +102,7 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stdout}\n{res.stderr}")
     os.replace(tmp, LIB)
+    call.result()       # the module's error, if any
     return LIB
 
 
