@@ -10,18 +10,24 @@
 //
 // Each function returns its outputs, the library's status as an int when the
 // library refused the call, or None when an argument is not what the fast path
-// takes (a wrong device, type, shape or stride, an explicit stream): qwam.py
-// then goes the long way, which names the argument that is wrong.
+// takes (a wrong device, type, shape or stride): qwam.py then goes the long
+// way, which names the argument that is wrong.  asp_linear and asp_layer go
+// there with an explicit stream too; an activation call does not, because the
+// workspace of its stream made it dearer there than without one (26 us of host
+// time against 16).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <c10/hip/HIPCachingAllocator.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
 #include <initializer_list>
+#include <memory>
 
 #include "../../include/qwam.h"
 
@@ -37,6 +43,7 @@ enum Attr { kK, kN, kR, kGroup, kHadamard, kWq, kWs, kInv, kL1t, kL2t, kBias, kL
 const char* const kAttrNames[kAttrs] = {"K",   "N",   "r",    "group", "hadamard", "wq",  "ws",
                                         "inv_smooth", "L1t", "L2t", "bias",  "L1",       "wsp", "L1f"};
 PyObject* g_names[kAttrs];
+PyObject *g_cuda_stream, *g_device_index;
 
 // the data pointer of a contiguous GPU tensor of this type and shape; false otherwise
 bool data_of(PyObject* o, at::ScalarType type, std::initializer_list<int64_t> shape, void** out) {
@@ -135,10 +142,21 @@ PyObject* none_or_error() {
 
 void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// quantize(layer, x, out, deflated) -> (xq, xs, t)
+// the handle of a torch.cuda.Stream of the current device; false for another device's
+bool stream_of(PyObject* o, hipStream_t* out) {
+  Held handle, device;
+  handle.o = PyObject_GetAttr(o, g_cuda_stream);
+  device.o = handle.o == nullptr ? nullptr : PyObject_GetAttr(o, g_device_index);
+  if (device.o == nullptr) return false;
+  *out = static_cast<hipStream_t>(PyLong_AsVoidPtr(handle.o));
+  const long index = PyLong_AsLong(device.o);
+  return !PyErr_Occurred() && index == c10::hip::current_device();
+}
+
+// quantize(layer, x, out, deflated, stream) -> (xq, xs, t); stream a torch.cuda.Stream or None
 PyObject* py_quantize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   HANDLE_TH_ERRORS
-  if (nargs != 4) Py_RETURN_NONE;
+  if (nargs != 5) Py_RETURN_NONE;
   Layer L;
   const int64_t M = rows_of(args[1]);
   void* x;
@@ -149,6 +167,10 @@ PyObject* py_quantize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     for (int i = 0; i < 3; ++i) given[i] = PyTuple_GET_ITEM(args[2], i);
   }
   const at::Tensor& xt = THPVariable_Unpack(args[1]);
+  hipStream_t given_stream = nullptr;
+  const bool explicit_stream = args[4] != Py_None;
+  if (explicit_stream && (!stream_of(args[4], &given_stream) || xt.get_device() != c10::hip::current_device()))
+    return none_or_error();
   Held xq, xs, t;
   void *pq, *ps, *pt;
   if (!output(given[0], xt, at::kByte, M, L.c.K / 2, &xq.o, &pq) ||
@@ -157,13 +179,19 @@ PyObject* py_quantize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     return none_or_error();
   const int32_t deflated = PyObject_IsTrue(args[3]) == 1;
   // few tokens and a large K: the call splits K over workgroups through a
-  // workspace, from the current stream's pool (dropped below: the next user of
-  // that memory runs behind the call's kernels)
+  // workspace, from the pool of the stream the call runs on (dropped below: the
+  // next user of that memory runs behind the call's kernels)
   const int64_t need = g_workspace(&L.c, static_cast<int32_t>(M), deflated);
   at::Tensor ws;
-  if (need > 0) ws = at::empty({need}, xt.options().dtype(at::kByte));
-  void* const pw = need > 0 ? ws.data_ptr() : nullptr;
-  void* stream = current_stream();
+  std::unique_ptr<void, void (*)(void*)> ws_stream(nullptr, c10::hip::HIPCachingAllocator::raw_delete);
+  if (need > 0) {
+    if (explicit_stream)
+      ws_stream.reset(c10::hip::HIPCachingAllocator::raw_alloc_with_stream(static_cast<size_t>(need), given_stream));
+    else
+      ws = at::empty({need}, xt.options().dtype(at::kByte));
+  }
+  void* const pw = need <= 0 ? nullptr : explicit_stream ? ws_stream.get() : ws.data_ptr();
+  void* stream = explicit_stream ? given_stream : current_stream();
   qwam_status st;
   Py_BEGIN_ALLOW_THREADS
   st = g_quantize(&L.c, static_cast<int32_t>(M), deflated, static_cast<const uint16_t*>(x), static_cast<uint8_t*>(pq),
@@ -243,5 +271,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_qwam_call", nullptr, -1, methods,
 PyMODINIT_FUNC PyInit__qwam_call() {
   for (int a = 0; a < kAttrs; ++a)
     if ((g_names[a] = PyUnicode_InternFromString(kAttrNames[a])) == nullptr) return nullptr;
+  if ((g_cuda_stream = PyUnicode_InternFromString("cuda_stream")) == nullptr ||
+      (g_device_index = PyUnicode_InternFromString("device_index")) == nullptr)
+    return nullptr;
   return PyModule_Create(&module);
 }

@@ -7,8 +7,9 @@ library is not built, every call raises: there is no fallback.
 
 The per-token calls (quantize_act, quantize_act_deflated, asp_linear,
 asp_layer) marshal natively (csrc/qwam_binding.cpp); what that path does not
-take (an explicit stream, or an argument that fails a check) goes through
-ctypes here, which raises for the argument that is wrong.
+take (for asp_linear and asp_layer an explicit stream, for all of them an
+argument that fails a check) goes through ctypes here, which raises for the
+argument that is wrong.
 
 Names follow the C ABI (include/qwam.h): pack_weights, quantize_act,
 quantize_act_deflated (both over qwam_quantize_act_ws), asp_linear, asp_layer, debug_group_partials,
@@ -239,15 +240,14 @@ def _workspace(nbytes: int, device, stream) -> Optional[torch.Tensor]:
         return None
     if stream is None:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
-    if not isinstance(stream, torch.cuda.Stream):
-        return None                       # a bare stream handle has no pool: the call runs unsplit
     with torch.cuda.stream(stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
 def _quantize(deflated: bool, name: str, layer: PackedLayer, x: torch.Tensor, stream, out):
-    if stream is None:
-        done = (_call or _native()).quantize(layer, x, out, deflated)
+    pooled = stream is None or isinstance(stream, torch.cuda.Stream)
+    if pooled:
+        done = (_call or _native()).quantize(layer, x, out, deflated, stream)
         if done is not None:
             if type(done) is int:
                 _check(name, done)
@@ -262,7 +262,8 @@ def _quantize(deflated: bool, name: str, layer: PackedLayer, x: torch.Tensor, st
         xq, xs, t = out
     c = layer.c_struct()
     # few tokens and a large K: the call splits K over workgroups through a workspace
-    need = lib().qwam_quantize_act_workspace(ctypes.byref(c), M, deflated)
+    # (a bare stream handle has no pool to take one from: the call runs unsplit)
+    need = lib().qwam_quantize_act_workspace(ctypes.byref(c), M, deflated) if pooled else 0
     ws = _workspace(need, dev, stream)
     st = lib().qwam_quantize_act_ws(ctypes.byref(c), M, deflated, _req(x, "x", torch.bfloat16, (M, layer.K)),
                                     _req(xq, "xq", torch.uint8, (M, layer.K // 2)),
