@@ -40,19 +40,21 @@ constexpr int32_t kMaxK = 65536;
 constexpr int32_t kMaxN = 1 << 20;
 constexpr int32_t kMaxM = 1 << 20;
 
-qwam_status check_kn(const char* fn, int32_t K, int32_t N, int32_t group) {
+// N is checked unless need_n is false (a call that does not read it)
+qwam_status check_kn(const char* fn, int32_t K, int32_t N, int32_t group, bool need_n = true) {
   if (group != QWAM_GROUP && group != 32)
     return fail(QWAM_ERR_INVALID_ARG, "%s: group must be 64 or 32 (got %d)", fn, group);
   if (K <= 0 || K % QWAM_GROUP != 0) return fail(QWAM_ERR_INVALID_ARG, "%s: K must be a positive multiple of 64 (got %d)", fn, K);
-  if (N <= 0 || N % 16 != 0) return fail(QWAM_ERR_INVALID_ARG, "%s: N must be a positive multiple of 16 (got %d)", fn, N);
+  if (need_n && (N <= 0 || N % 16 != 0))
+    return fail(QWAM_ERR_INVALID_ARG, "%s: N must be a positive multiple of 16 (got %d)", fn, N);
   if (K > kMaxK) return fail(QWAM_ERR_UNSUPPORTED, "%s: K = %d exceeds %d", fn, K, kMaxK);
-  if (N > kMaxN) return fail(QWAM_ERR_UNSUPPORTED, "%s: N = %d exceeds %d", fn, N, kMaxN);
+  if (need_n && N > kMaxN) return fail(QWAM_ERR_UNSUPPORTED, "%s: N = %d exceeds %d", fn, N, kMaxN);
   return QWAM_OK;
 }
 
-qwam_status check_layer(const char* fn, const qwam_layer* L, bool need_branch) {
+qwam_status check_layer(const char* fn, const qwam_layer* L, bool need_branch, bool need_n = true) {
   if (L == nullptr) return fail(QWAM_ERR_INVALID_ARG, "%s: layer is NULL", fn);
-  qwam_status s = check_kn(fn, L->K, L->N, L->group);
+  qwam_status s = check_kn(fn, L->K, L->N, L->group, need_n);
   if (s != QWAM_OK) return s;
   if (need_branch && !(L->r == 16 || L->r == 32 || L->r == 48 || L->r == 64))
     return fail(QWAM_ERR_UNSUPPORTED, "%s: rank r must be 16, 32, 48 or 64 (got %d)", fn, L->r);
@@ -166,7 +168,7 @@ qwam_status qwam_quantize_act_deflated(const qwam_layer* L, int32_t M, const uin
 
 int64_t qwam_quantize_act_workspace(const qwam_layer* L, int32_t M, int32_t deflated) {
   const char* fn = "qwam_quantize_act_workspace";
-  if (check_layer(fn, L, true) != QWAM_OK || check_m(fn, M) != QWAM_OK) return -1;
+  if (check_layer(fn, L, true, false) != QWAM_OK || check_m(fn, M) != QWAM_OK) return -1;
   return qwam::act_workspace_bytes(M, L->K, L->r, L->hadamard, deflated != 0);
 }
 

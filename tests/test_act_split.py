@@ -56,6 +56,16 @@ def test_workspace_query_and_checks(lib):
     assert call(FAKE + 8, n) == 3
 
 
+def test_workspace_query_reads_only_its_fields(lib):
+    """K, r, group and hadamard of the layer, as the header says: the others may be unset."""
+    for kw in (dict(K=14336), dict(K=14336, r=48, group=32, hadamard=1024)):
+        c = Q.QwamLayerC()
+        c.K, c.r, c.group, c.hadamard = kw["K"], kw.get("r", 32), kw.get("group", 64), kw.get("hadamard", 0)
+        for defl in (0, 1):
+            assert lib.qwam_quantize_act_workspace(ctypes.byref(c), 33, defl) == \
+                lib.qwam_quantize_act_workspace(ctypes.byref(_c(**kw)), 33, defl) > 0
+
+
 CASES = [
     # M, K, r, group, rotated
     (1, 3072, 16, 64, False),
