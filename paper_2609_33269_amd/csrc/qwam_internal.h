@@ -46,7 +46,7 @@ constexpr int kSplitBlocks = 128;
 constexpr int kMinUnits = 12, kMinUnitsDeflated = 6;
 constexpr int kMinTiles = 2;
 ActSplit act_split(int M, int K, int unit_groups, int min_units);
-ActSplit rotated_split(int M, int K, int r, int B);
+ActSplit rotated_split(int M, int K, int r, int B, bool deflate);
 int64_t act_workspace_bytes(int M, int K, int r, int B, bool deflate);
 hipError_t launch_split_t(int M, int r, int splits, const float* part, uint16_t* t, hipStream_t stream);
 

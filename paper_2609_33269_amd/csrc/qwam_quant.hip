@@ -382,7 +382,7 @@ static int64_t split_bytes(const ActSplit& s, int M, int r, size_t elem) {
 }
 
 int64_t act_workspace_bytes(int M, int K, int r, int B, bool deflate) {
-  const ActSplit s = B != 0 ? rotated_split(M, K, r, B)
+  const ActSplit s = B != 0 ? rotated_split(M, K, r, B, deflate)
                             : act_split(M, K, 4, deflate ? kMinUnitsDeflated : kMinUnits);
   return s.splits > 1 ? split_bytes(s, M, r, deflate ? sizeof(double) : sizeof(float)) : 0;
 }

@@ -553,21 +553,42 @@ __global__ __launch_bounds__(256) void quantize_act_rotated_few_kernel(
   }
 }
 
-// Tile width: the largest multiple of max(B, 64) that divides K and is at
-// most 1024.
-static int rotate_tile_width(int K, int B) {
+// LDS of a workgroup of the tile kernel: two tiles, then the partial t tiles
+// (`sums`: not in the launch of the codes alone), or those over a tile buffer
+// when all of it would not fit (and they fit in a tile), then -t (deflated).
+constexpr size_t kLdsBytes = 160 * 1024;
+struct RotLds {
+  size_t tile, total;
+  bool over;                    // partial t tiles over a tile buffer
+};
+static RotLds rotate_lds(int T, int r, bool deflate, bool sums) {
+  const int nwaves = r <= 32 ? act_waves<32>() : act_waves<64>();
+  RotLds l;
+  l.tile = static_cast<size_t>(16) * (T + kTilePad) * sizeof(float);
+  const size_t red = sums ? static_cast<size_t>(nwaves) * 16 * r * (deflate ? sizeof(double) : sizeof(float)) : 0;
+  const size_t tneg = deflate ? 16 * r * sizeof(float) : 0;
+  l.over = 2 * l.tile + red + tneg > kLdsBytes && red <= l.tile;
+  l.total = 2 * l.tile + (l.over ? 0 : red) + tneg;
+  return l;
+}
+
+// Tile width: the largest multiple of max(B, 64) that divides K, is at most
+// 1024 and fits in LDS with the partial t tiles (deflated at r = 32 and 64,
+// widths of 768 to 960 do not: 64 KB of double partials, larger than a tile of
+// them and too large beside two; B itself, at most 512 or 1024, always fits).
+static int rotate_tile_width(int K, int B, int r, bool deflate) {
   const int base = B > kGroup ? B : kGroup;
   for (int c = 1024 / base; c > 1; --c)
-    if ((K / base) % c == 0) return base * c;
+    if ((K / base) % c == 0 && rotate_lds(base * c, r, deflate, true).total <= kLdsBytes) return base * c;
   return base;
 }
 
 // few tokens: one workgroup per token (r = 16 up to K = 2048, r = 32 up to K = 1024)
 static bool rotate_few(int M, int K, int r) { return M <= kFewTokens && (r == 16 || r == 32) && K * r <= 256 * 128; }
 
-ActSplit rotated_split(int M, int K, int r, int B) {
+ActSplit rotated_split(int M, int K, int r, int B, bool deflate) {
   if (rotate_few(M, K, r)) return {0, 0};
-  const int T = rotate_tile_width(K, B);
+  const int T = rotate_tile_width(K, B, r, deflate);
   return act_split(M, K, T / kGroup, kMinTiles);
 }
 
@@ -578,7 +599,7 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
   int logB = 0;
   while ((1 << logB) < B) ++logB;
   if ((1 << logB) != B || B < 16 || B > 1024 || K % B != 0) return hipErrorInvalidValue;
-  const int T = rotate_tile_width(K, B);
+  const int T = rotate_tile_width(K, B, r, deflate);
   // a tile has at most 16 passes / groups: per_wave<r>() per wave
   if (T / kGroup > 16) return hipErrorInvalidValue;
   const float hscale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(B)));
@@ -598,23 +619,17 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
     QWAM_FEW(32, 256) QWAM_FEW(32, 512) QWAM_FEW(32, 1024)
 #undef QWAM_FEW
   }
-  const ActSplit split = workspace != nullptr ? rotated_split(M, K, r, B) : ActSplit{0, 0};
+  const ActSplit split = workspace != nullptr ? rotated_split(M, K, r, B, deflate) : ActSplit{0, 0};
   const bool splits = split.splits > 1;
   const int tiles_per_wg = splits ? split.groups * kGroup / T : K / T;
   auto go = [&](auto kernel, int nwaves, auto* part, bool sums) {
-    // two tiles, then the partial t tiles (not in the launch of the codes
-    // alone), or those over a tile buffer when all of it would not fit in LDS
-    // (and they fit in a tile)
-    const size_t tile_bytes = static_cast<size_t>(16) * (T + kTilePad) * sizeof(float);
-    const size_t red_bytes = sums ? static_cast<size_t>(nwaves) * 16 * r * sizeof(*part) : 0;
-    const size_t tneg_bytes = deflate ? 16 * r * sizeof(float) : 0;
-    const bool over = 2 * tile_bytes + red_bytes + tneg_bytes > 160 * 1024 && red_bytes <= tile_bytes;
+    const RotLds l = rotate_lds(T, r, deflate, sums);
     // over a tile: the buffer the last tile does not use (the deflated
     // variant's second pass reads that tile again)
     const int last_buf = (tiles_per_wg - 1) & 1;
-    const int red_off = static_cast<int>((over ? 1 - last_buf : 2) * tile_bytes / sizeof(float));
-    const size_t lds = 2 * tile_bytes + (over ? 0 : red_bytes) + tneg_bytes;
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    const int red_off = static_cast<int>((l.over ? 1 - last_buf : 2) * l.tile / sizeof(float));
+    const size_t lds = l.total;
+    if (lds > kLdsBytes) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));

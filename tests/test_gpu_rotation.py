@@ -120,6 +120,23 @@ def test_rotated_few_tokens(M, K, N, r, bias, deflate):
     _rotated_parity(d, oracle_factors(d, r, hadamard=True), d.bias, deflate=deflate)
 
 
+# M, K, N, r, bias: the widest tile that divides K (768 to 960 channels) has no room in LDS beside the double partials
+NARROWED_TILE_SHAPES = [
+    (65, 768, 48, 32, True),     # B 256, T 256
+    (70, 960, 32, 64, False),    # B 64,  T 320
+    (17, 2304, 32, 64, True),    # B 256, T 256
+    (33, 3840, 64, 32, False),   # B 256, T 256
+    (66, 896, 32, 32, False),    # B 128, T 128
+    (2100, 768, 16, 32, False),  # T 256, more token blocks than the split takes
+]
+
+
+@pytest.mark.parametrize("M,K,N,r,bias", NARROWED_TILE_SHAPES)
+def test_rotated_deflated_narrowed_tiles(M, K, N, r, bias):
+    d = I.custom(M, K, N, r, seed=29 * M + K, n_outliers=4, with_bias=bias)
+    _rotated_parity(d, oracle_factors(d, hadamard=True), d.bias, deflate=True)
+
+
 def test_rotated_one_hot_closed_form():
     """x = e_k (lambda = 1, B = 1024): the rotated token is +-2^-5 on the whole
     block, so every code of that block is +-7 with the sign of row k of H and
