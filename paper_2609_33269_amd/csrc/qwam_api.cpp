@@ -9,6 +9,7 @@
 #include <cstdio>
 
 #include "../../include/qwam.h"
+#include "../../include/qwam_probe.h"
 #include "qwam_internal.h"
 
 namespace {
@@ -201,6 +202,20 @@ qwam_status qwam_asp_linear(const qwam_layer* L, int32_t M, const uint8_t* xq, c
   if ((s = check_device(fn)) != QWAM_OK) return s;
   return launched(fn, qwam::launch_asp_gemm(M, L->N, L->K, L->r, L->group, xq, xs, t, L->wq, L->ws, L->wsp, L->L2t,
                                             L->bias, y, static_cast<hipStream_t>(stream)));
+}
+
+int32_t qwam_probe_gemm_form(int32_t M, int32_t N, int32_t K, int32_t group) {
+  const char* fn = "qwam_probe_gemm_form";
+  if (check_kn(fn, K, N, group) != QWAM_OK || check_m(fn, M) != QWAM_OK) return -1;
+  if (M <= qwam::kSmallM) return QWAM_PROBE_GEMM_FEW;
+  switch (qwam::gemm_form(M, N, K, group)) {
+    case qwam::GemmForm::kLarge: return QWAM_PROBE_GEMM_LARGE;
+    case qwam::GemmForm::kLargeSplit: return QWAM_PROBE_GEMM_LARGE_HALVES;
+    case qwam::GemmForm::k32x64Waves8: return QWAM_PROBE_GEMM_32X64_W8;
+    case qwam::GemmForm::k32x64Waves4: return QWAM_PROBE_GEMM_32X64_W4;
+    case qwam::GemmForm::k64x64Waves4: return QWAM_PROBE_GEMM_64X64_W4;
+  }
+  return -1;
 }
 
 qwam_status qwam_debug_group_partials(const qwam_layer* L, int32_t M, const uint8_t* xq, int32_t* P,

@@ -691,15 +691,34 @@ static hipError_t launch_asp_gemm_gs(int M, int N, int K, int r, const uint8_t* 
 // workgroups fit two to a CU runs in rounds of 512 tiles; a last round of at
 // most 256 leaves each CU one tile and is shorter.  Each round costs a start-up
 // and a part in proportion to K; the constants (in ns and ns per 1024
-// channels) are least-squares fits, mean error 3-5%, of all forms timed at
-// several hundred shapes (M = 65 .. 3000, K = 576 .. 14336, N = 1024 .. 9216,
-// both group sizes).  Large tiles / choice at group 64: M = 100, K = N = 3072
-// 18.9 / 6.2 us; M = 415, K = 14336, N = 3072 75.7 / 35.7 us; M = 512, K = 576,
-// N = 3072 8.1 / 6.9 us; M = 333, K = 3072, N = 9216 22.2 / 20.6 us (K split in
-// the large tile); M = 4096 always the large tiles.  The large tiles keep
-// calls within 3% of their estimate, and within 8% once they have more tiles
-// than CUs: there the small tiles' extra traffic showed up to 20% above
-// their estimate (M = 2048, K = 7168, N = 3072: 64 / 77 us, estimated 63 / 61).
+// channels) are least-squares fits of all forms timed at several hundred
+// shapes (M = 65 .. 3000, K = 576 .. 14336, N = 1024 .. 9216, both group
+// sizes).  Large tiles / choice at group 64: M = 100, K = N = 3072 18.9 / 6.2
+// us; M = 415, K = 14336, N = 3072 75.7 / 35.7 us; M = 512, K = 576, N = 3072
+// 8.1 / 6.9 us; M = 333, K = 3072, N = 9216 22.2 / 20.6 us (K split in the
+// large tile); M = 4096 always the large tiles.
+//
+// Against 23000 random shapes (M = 65 .. 8192, K = 64 .. 14336, N = 16 .. 14336,
+// every rank) the estimates are wrong at the edges of the fit, where the lines
+// below hold them back: with them 0.7% of the choices of another form are more
+// than 3% slower than the large tiles (without: 5.5%, up to 46%), and the choice
+// is 0.8% slower than the best form on average (1.2%).  The large tiles keep a
+// call
+//   * within 3% of their estimate, and within 8% once they have more tiles
+//     than CUs;
+//   * within 20%, against the small tiles at group 64, above 3000 tokens (more
+//     than the fit has seen) with more than 128 large tiles: each XCD's small
+//     tiles read all of the activations, which do not stay in its L2 (M = 7976,
+//     K = 3136, N = 352: 23.3 / 28.9 us);
+//   * when K is one stage (256 channels; group 64: up to 192) and the small tiles
+//     are more than a round: one of a tile's waves has work, so a second
+//     tile on a CU adds its whole time (group 32, K = 256: 32 x 64 tiles in
+//     their second round 7.0 / 8.5 us, 64 x 64 tiles two to a CU 7.0 / 7.7 us,
+//     beyond 9.9 / 15.3 us), and at group 32 up to 512 channels when the large
+//     tiles are more than CUs too (14.2 / 18.8 us);
+//   * against K in two halves, at group 64 below K = 2816 (4-9% slower there;
+//     from 3072 on 2-10% faster, at group 32 from 1024 on 2-23%).  The
+//     halves are whole stages, so an odd number of stages costs one more.
 struct FormCost {
   int start, round, round_k, last, last_k;   // last, last_k: a last round of at most 256 tiles
 };
@@ -713,22 +732,29 @@ static int64_t form_ns(const FormCost& c, int64_t tiles, int per_cu, int K) {
   return ns;
 }
 
-static GemmForm gemm_form(int M, int N, int K, int group) {
+GemmForm gemm_form(int M, int N, int K, int group) {
   // in the order of GemmForm
   static const FormCost cost[2][5] = {
       {{2160, 5320, 8000, 3700, 5030}, {900, 5900, 4040, 0, 0}, {1930, 2370, 860, 0, 0}, {2660, 1960, 1500, 1240, 1030},
        {2580, 2800, 2360, 1780, 1560}},
       {{2670, 7230, 13090, 3170, 10500}, {1800, 5350, 7150, 0, 0}, {1890, 2520, 1300, 0, 0}, {2980, 1910, 2280, 970, 1420},
        {3030, 3210, 3960, 1850, 2750}}};
-  const FormCost* c = cost[group == 32 ? 1 : 0];
+  const bool g32 = group == 32;
+  const FormCost* c = cost[g32 ? 1 : 0];
   const auto tiles = [&](int tm, int tn) { return static_cast<int64_t>((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-  const int64_t large = tiles(BM, BN);
-  const int64_t ns[5] = {form_ns(c[0], large, 2, K), form_ns(c[1], large, 1, K), form_ns(c[2], tiles(32, 64), 1, K),
-                         form_ns(c[3], tiles(32, 64), 2, K), form_ns(c[4], tiles(64, 64), 2, K)};
-  const int64_t keep = ns[0] - ns[0] / (large > 256 ? 12 : 32);
+  const int64_t large = tiles(BM, BN), t32 = tiles(32, 64), t64 = tiles(64, 64);
+  const int halves_k = (K + 8 * kGroup - 1) / (8 * kGroup) * (8 * kGroup);
+  const int64_t ns[5] = {form_ns(c[0], large, 2, K), form_ns(c[1], large, 1, halves_k), form_ns(c[2], t32, 1, K),
+                         form_ns(c[3], t32, 2, K), form_ns(c[4], t64, 2, K)};
+  const bool one_stage = K <= (g32 ? 256 : 192);
+  const bool short_k = g32 && K <= 512 && large > 256;
+  const bool usable[5] = {true, K >= (g32 ? 1024 : 2816), !short_k && (!one_stage || t32 <= 256),
+                          !short_k && (!one_stage || t32 <= 512), !short_k && (!one_stage || t64 <= 256)};
+  const int64_t keep_halves = ns[0] - ns[0] / (large > 256 ? 12 : 32);
+  const int64_t keep_small = !g32 && M > 3000 && large > 128 ? ns[0] - ns[0] / 5 : keep_halves;
   int best = 0;
-  for (int i = K >= 1024 ? 1 : 2; i < 5; ++i)   // (two halves of a shorter K are all start-up)
-    if (ns[i] < (best == 0 ? keep : ns[best])) best = i;
+  for (int i = 1; i < 5; ++i)
+    if (usable[i] && ns[i] < (i == 1 ? keep_halves : keep_small) && (best == 0 || ns[i] < ns[best])) best = i;
   return static_cast<GemmForm>(best);
 }
 

@@ -82,6 +82,7 @@ hipError_t launch_asp_gemm_small(int M, int N, int K, int r, int group, const ui
 // x 64 channels with K split over the workgroup's waves (for a few hundred
 // tokens)
 enum class GemmForm { kLarge = 0, kLargeSplit = 1, k32x64Waves8 = 2, k32x64Waves4 = 3, k64x64Waves4 = 4 };
+GemmForm gemm_form(int M, int N, int K, int group);
 hipError_t launch_asp_gemm_mid(GemmForm form, int M, int N, int K, int r, int group, const uint8_t* xq,
                                const float* xs, const uint16_t* t, const uint8_t* wq, const uint32_t* wsp,
                                const uint16_t* L2t, const uint16_t* bias, uint16_t* y, hipStream_t stream);

@@ -14,7 +14,7 @@ argument that is wrong.
 Names follow the C ABI (include/qwam.h): pack_weights, quantize_act,
 quantize_act_deflated (both over qwam_quantize_act_ws), asp_linear, asp_layer, debug_group_partials,
 aog_accumulate, aog_protected_basis; and the measurement probes of include/qwam_probe.h:
-probe_mfma, probe_valu_fma, probe_copy, probe_empty.
+probe_mfma, probe_valu_fma, probe_copy, probe_empty, probe_gemm_form.
 """
 
 from __future__ import annotations
@@ -70,6 +70,7 @@ SIGNATURES = {
     "qwam_probe_valu_fma": (ctypes.c_int, [_i32, _i32, _c_void_p, _c_void_p]),
     "qwam_probe_copy": (ctypes.c_int, [_c_void_p, _c_void_p, ctypes.c_int64, _i32, _c_void_p]),
     "qwam_probe_empty": (ctypes.c_int, [_c_void_p]),
+    "qwam_probe_gemm_form": (_i32, [_i32, _i32, _i32, _i32]),
     "qwam_probe_last_error": (ctypes.c_char_p, []),
     "qwam_status_string": (ctypes.c_char_p, [ctypes.c_int]),
     "qwam_abi_version": (ctypes.c_int32, []),
@@ -425,3 +426,14 @@ def probe_copy(src: torch.Tensor, dst: torch.Tensor, workgroups: int = 4096, str
 def probe_empty(stream=None) -> None:
     """qwam_probe_empty: one empty launch."""
     _probe_check("qwam_probe_empty", lib().qwam_probe_empty(_stream_ptr(stream)))
+
+
+GEMM_FORMS = ("few", "128x128", "128x128 halves", "32x64 w8", "32x64 w4", "64x64 w4")   # QWAM_PROBE_GEMM_*
+
+
+def probe_gemm_form(M: int, N: int, K: int, group: int = GROUP) -> str:
+    """qwam_probe_gemm_form: the kernel asp_linear runs at these sizes (on the host, nothing is launched)."""
+    form = lib().qwam_probe_gemm_form(M, N, K, group)
+    if form < 0:
+        raise QwamError("qwam_probe_gemm_form", 2, lib().qwam_last_error().decode())
+    return GEMM_FORMS[form]
