@@ -197,7 +197,7 @@ def check_y_per_token(y_gpu_bits, y_ref, abs_terms, n_groups, rank):
 def sample_rows(M: int, seed: int, extra: int = 64) -> np.ndarray:
     """Token sample of a large layer: the first and last token, one token in
     every 128-token tile and `extra` more at random; more than 64 tokens for
-    M >= 128, so that the debug partials run on the large-tile GEMM."""
+    M >= 128, so that the debug partials run on the 128 x 128 tiles."""
     rng = np.random.default_rng(seed)
     rows = {0, M - 1}
     for tile in range(0, M, 128):

@@ -5,8 +5,9 @@ Bit-exact: weight and activation codes, bytes and scales, the int32 group
 partials (two per 64-channel span, each from its own matrix-core pass), and
 with deflation also t.  y within the relative Frobenius tolerance of
 parity_helpers.check_y of the float64 oracle on the same codes.  Covers the
-large-tile GEMM (M > 64) and the few-token GEMM (M <= 64), and the plain,
-deflated and rotated activation kernels.
+32 x 64 and 128 x 128 tile GEMMs (M > 64; their edges: test_gpu_gemm_forms.py)
+and the few-token GEMM (M <= 64), and the plain, deflated and rotated
+activation kernels.
 """
 
 import numpy as np
@@ -60,13 +61,13 @@ G32_SHAPES = [
     (1, 64, 16, 16, False),
     (15, 128, 48, 32, True),
     (64, 1024, 4096, 16, False),     # the few-token GEMM at an action-expert shape
-    (65, 192, 144, 48, True),        # the large-tile GEMM from M = 65 on
+    (65, 192, 144, 48, True),        # 32 x 64 tiles from M = 65 on
     (129, 256, 272, 64, False),
     (200, 320, 400, 32, True),
     (257, 640, 256, 32, False),
-    (130, 65536, 64, 16, True),      # the largest K, large-tile GEMM
+    (130, 65536, 64, 16, True),      # the largest K, 32 x 64 tiles
     (1 << 20, 64, 16, 16, False),    # the largest M
-    (65, 64, 1 << 20, 16, False),    # the largest N, large-tile GEMM
+    (65, 64, 1 << 20, 16, False),    # the largest N, 128 x 128 tiles
 ]
 
 

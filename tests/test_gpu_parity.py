@@ -69,15 +69,15 @@ EDGE_SHAPES = [
     (17, 192, 144, 48, False),
     (129, 256, 272, 64, True),
     (200, 320, 400, 32, False),
-    (97, 192, 176, 48, True),        # r = 48 on the large-tile GEMM, ragged N, bias
+    (97, 192, 176, 48, True),        # r = 48, 32 x 64 tiles, ragged N, bias
     (130, 1024, 1040, 16, True),
     (257, 640, 256, 32, False),
     (33, 16448, 64, 32, False),      # K > 16384: 1/lambda read from global memory
     # the largest sizes the entry points take
-    (130, 65536, 64, 16, True),      # K = 65536, the large-tile GEMM
+    (130, 65536, 64, 16, True),      # K = 65536, 32 x 64 tiles
     (1, 64, 1 << 20, 16, False),     # N = 2^20, one token
     (1 << 20, 64, 16, 16, False),    # M = 2^20
-    (65, 64, 1 << 20, 16, False),    # N = 2^20 on the large-tile GEMM
+    (65, 64, 1 << 20, 16, False),    # N = 2^20, 128 x 128 tiles
 ]
 
 
@@ -125,7 +125,7 @@ def _large_parity(draws, extra_rows=64):
     """Full-size layer in the benchmark's launch configuration: every code,
     scale and t element is checked; y (whole sample, every token, every
     element) and the partials on sampled tokens (more than 64, so the
-    partials come from the large-tile GEMM)."""
+    partials come from the 128 x 128 tiles)."""
     M, K, N = draws.shape.M, draws.shape.K, draws.shape.N
     log(f"  large parity {draws.shape.name}: M={M} K={K} N={N} r={draws.shape.r}")
     f = oracle_factors(draws)
@@ -169,7 +169,7 @@ def test_denoise_step_sampled_layers(block, which):
 
 def test_repeat_runs_bit_identical():
     """Determinism / race proxy: 20 runs of every kernel of the layer (the
-    large-tile GEMM, its debug partials, the few-token GEMM and the fused
+    32 x 64 tile GEMM, the debug partials, the few-token GEMM and the fused
     layer) on four streams, in varied launch orders and with the outputs of
     several runs in flight at once, give bit-identical codes, scales, t,
     partials and y."""
