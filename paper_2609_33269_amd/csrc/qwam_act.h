@@ -268,7 +268,8 @@ __device__ __forceinline__ void combine_split_t(const double* __restrict__ part,
 }
 
 // Which part of the deflated computation a launch does: all of it (K not
-// split), the partial sums of t, or the deflation and the codes.
-enum class Phase { kAll, kSums, kCodes };
+// split; kOneTile: where K is one tile of the rotated kernel), the partial sums
+// of t, or the deflation and the codes.
+enum class Phase { kAll, kSums, kCodes, kOneTile };
 
 }  // namespace qwam

@@ -65,8 +65,9 @@ __device__ __forceinline__ int rot_chunk(int lane) { return lane ^ ((lane & 4) ?
 //              subtraction serve two elements.  Register bit 2 (3) and lane bit
 //              4 (5) trade places; rot_element gives the resulting element.
 // 11 vector instructions per element (18 and an LDS swizzle with a separate
-// exchange per element): M = 4096, r = 32, rotated 20.8 -> 17.6 us (K = 3072)
-// and 82 -> 72 us (K = 14336), rotated and deflated 52 -> 45 and 219 -> 186 us.
+// exchange per element): M = 4096, r = 32, rotated 20.1 -> 15.9 us (K = 3072)
+// and 79 -> 66 us (K = 14336), rotated and deflated 50 -> 41 and 224 -> 179 us;
+// where every pass holds a -0, 18.0, 71, 45 and 201 us.
 //
 // v <- v + s (v of the lane that `ctrl` names), for eight registers in one
 // instruction each (the compiler keeps the exchange and the multiply-add
@@ -168,12 +169,27 @@ constexpr int per_wave() { return 16 / act_waves<RANK>(); }
 // operations only, so prefetched global loads stay in flight across it.
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Row of the [16][T] tile that holds 16-element chunk c: c / (T / 16), as one
+// multiplication and a shift.  T is no constant and often no power of two; a
+// division and a remainder per tile address, five pairs a pass, cost up to 1 us a
+// tile (M = 300, K = 320, r = 16, deflated: 7.9 us, as it is 6.1).  Every chunk of
+// every width is checked below.
+constexpr int tile_row_mul(int T) { return (65536 + T / 16 - 1) / (T / 16); }
+constexpr int tile_row(int c, int mul) { return (c * mul) >> 16; }
+constexpr bool tile_rows_exact() {
+  for (int T = 64; T <= 1024; T += 64)
+    for (int c = 0; c < T; ++c)
+      if (tile_row(c, tile_row_mul(T)) != c / (T / 16)) return false;
+  return true;
+}
+static_assert(tile_rows_exact(), "the multiplication gives the quotient");
+
 template <int RANK, bool DEFLATE, Phase PHASE>
 __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_kernel(
     const uint16_t* __restrict__ x, const float* __restrict__ inv_smooth,
     const uint16_t* __restrict__ L1f, const uint16_t* __restrict__ L1, uint8_t* __restrict__ xq, float* __restrict__ xs,
     uint16_t* __restrict__ t, std::conditional_t<DEFLATE, double, float>* __restrict__ part, int M, int K, int logB,
-    int T, float hscale, int g32, int red_off, int tiles_per_wg) {
+    int T, int row_mul, float hscale, int g32, int red_off, int tiles_per_wg) {
   static_assert(DEFLATE || PHASE == Phase::kAll, "one launch without deflation");
   constexpr int RB = RANK / 16;
   constexpr int kMaxPerWave = per_wave<RANK>();
@@ -193,7 +209,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
   const int rows = min(16, M - m0);
   const int TS = T + kTilePad;
   const int tile0 = static_cast<int>(blockIdx.y) * tiles_per_wg;   // the workgroup's tiles (all of them, or a split)
-  const int ntiles = min(K / T - tile0, tiles_per_wg);
+  const int ntiles = PHASE == Phase::kOneTile ? 1 : min(K / T - tile0, tiles_per_wg);
   const int npass = T / kGroup;          // 1024-element passes per tile = groups per tile
 
   float* tiles = reinterpret_cast<float*>(lds_raw);
@@ -211,9 +227,10 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
     for (int k = 0; k < kMaxPerWave; ++k) {
       const int p = wave + k * nwaves;
       if (p < npass) {
-        const int e = p * 1024 + 16 * rot_chunk(lane);
-        const int ch = (tile0 + tb) * T + e % T;
-        const uint32_t xo = static_cast<uint32_t>((e / T) * K + ch) * 2u;
+        const int c = p * 64 + rot_chunk(lane);
+        const int r = tile_row(c, row_mul);
+        const int ch = (tile0 + tb) * T + 16 * c - r * T;
+        const uint32_t xo = static_cast<uint32_t>(r * K + ch) * 2u;
         rf[k].xa = buf_load16(x_rsrc, xo);
         rf[k].xb = buf_load16(x_rsrc, xo + 16u);
         const float4* ip = reinterpret_cast<const float4*>(inv_smooth + ch);
@@ -231,20 +248,37 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
         // The lane's signs and addresses do not change from tile to tile.  Kept
         // in registers (128 at 16 waves) they make the variant without
         // deflation spill, which then takes 83 instead of 74 us at M = 4096,
-        // K = 14336; the deflated one keeps them (182 against 197 us).
+        // K = 14336; the deflated one keeps them (178 against 189 us), except
+        // where there is only one tile (kOneTile: the set-up ahead of the loop
+        // took longer than it saved, M = 300, K = 320, r = 16 6.7 us).
         int ln = lane;
         if constexpr (!DEFLATE) asm volatile("" : "+v"(ln));
         float v[16];
         smooth16_regs(rf[k].xa, rf[k].xb, rf[k].inv, v);
         if (any_negative_zero(v)) fwht16<true>(v, ln, logB, hscale);
         else fwht16<false>(v, ln, logB, hscale);
+        // float offsets of the four quads in the tile; blocks of up to 256 keep
+        // a lane's elements in one chunk, whose row is computed once
+        int off[4];
+        if (logB > 8) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int e = p * 1024 + rot_element(ln, q, logB);
-          const int ch = e % T;
-          *reinterpret_cast<float4*>(tile + (e / T) * TS + (ch & ~15) + 4 * (((ch >> 2) & 3) ^ tile_swz(ch >> 4))) =
-              make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+          for (int q = 0; q < 4; ++q) {
+            const int e = p * 1024 + rot_element(ln, q, logB);
+            const int r = tile_row(e >> 4, row_mul);
+            const int ch = e - r * T;
+            off[q] = r * TS + (ch & ~15) + 4 * (((ch >> 2) & 3) ^ tile_swz(ch >> 4));
+          }
+        } else {
+          const int c = p * 64 + rot_chunk(ln);
+          const int r = tile_row(c, row_mul);
+          const int ch = 16 * c - r * T;
+          const int sw = tile_swz(ch >> 4);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) off[q] = r * TS + ch + 4 * (q ^ sw);
         }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(tile + off[q]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
       }
     }
   };
@@ -327,7 +361,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_rotated_k
     const float* tn_row = tneg + row * RANK;
     // (A launch of its own for the codes, kCodes, has no tile in LDS: it
     // rotates tiles 0, 1, .. in order.)
-    constexpr bool kept = PHASE == Phase::kAll;
+    constexpr bool kept = PHASE != Phase::kCodes;
     const int Lb = (ntiles - 1) & 1;
     for (int i = 0; i < ntiles; ++i) {
       const int tb = !kept ? i : i == 0 ? ntiles - 1 : i - 1;
@@ -636,7 +670,8 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
       if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kernel, dim3((M + 15) / 16, splits ? split.splits : 1), dim3(64 * nwaves), lds, stream, x, inv_smooth,
-                       L1f, L1, xq, xs, t, splits ? part : nullptr, M, K, logB, T, hscale, group == 32 ? 1 : 0, red_off,
+                       L1f, L1, xq, xs, t, splits ? part : nullptr, M, K, logB, T, tile_row_mul(T),
+                       hscale, group == 32 ? 1 : 0, red_off,
                        tiles_per_wg);
     return hipGetLastError();
   };
@@ -648,7 +683,9 @@ hipError_t launch_quantize_act_rotated(int M, int K, int r, int group, int B, bo
       const hipError_t e = go(quantize_act_rotated_kernel<R, false, Phase::kAll>, act_waves<R>(), pf, true);        \
       return e != hipSuccess || !splits ? e : launch_split_t(M, R, split.splits, pf, t, stream);                    \
     }                                                                                                               \
-    if (!splits) return go(quantize_act_rotated_kernel<R, true, Phase::kAll>, act_waves<R>(), pd, true);            \
+    if (!splits)                                                                                                    \
+      return T == K ? go(quantize_act_rotated_kernel<R, true, Phase::kOneTile>, act_waves<R>(), pd, true)           \
+                    : go(quantize_act_rotated_kernel<R, true, Phase::kAll>, act_waves<R>(), pd, true);              \
     const hipError_t e = go(quantize_act_rotated_kernel<R, true, Phase::kSums>, act_waves<R>(), pd, true);          \
     return e != hipSuccess ? e : go(quantize_act_rotated_kernel<R, true, Phase::kCodes>, act_waves<R>(), pd, false);  \
   }
