@@ -42,9 +42,13 @@ struct ActSplit {
 // deflated K = 2048 27.8 / 20.2 us, K = 14336 173 / 22.2 us.  2048 tokens (two
 // splits), K = 14336: 29.8 / 21.6, 119 / 68, 61 / 36 and 177 / 104 us.  As many
 // splits as one round of 256 workgroups holds: 384 to 768 took 10-30% longer.
+// Plain calls of 16 waves a workgroup (r <= 32) that only get two splits (above
+// 1360 tokens) need a longer K: 12-13 units 9.0 / 9.8 us, 14-15 units 10.2 /
+// 10.4, 16 units 11.2 / 10.8 us (of 8 waves, r = 48 and 64: 11.6 / 10.7 us at 12).
 constexpr int kSplitBlocks = 128;
-constexpr int kMinUnits = 12, kMinUnitsDeflated = 6;
+constexpr int kMinUnits = 12, kMinUnitsTwo = 16, kMinUnitsDeflated = 6;
 constexpr int kMinTiles = 2;
+int plain_min_units(int M, int r);
 ActSplit act_split(int M, int K, int unit_groups, int min_units);
 ActSplit rotated_split(int M, int K, int r, int B, bool deflate);
 int64_t act_workspace_bytes(int M, int K, int r, int B, bool deflate);

@@ -377,13 +377,17 @@ ActSplit act_split(int M, int K, int unit_groups, int min_units) {
   return {(units + per - 1) / per, per * unit_groups};
 }
 
+int plain_min_units(int M, int r) {
+  return r <= 32 && 256 / ((M + 15) / 16) <= 2 ? kMinUnitsTwo : kMinUnits;
+}
+
 static int64_t split_bytes(const ActSplit& s, int M, int r, size_t elem) {
   return static_cast<int64_t>(s.splits) * ((M + 15) / 16 * 16) * r * static_cast<int64_t>(elem);
 }
 
 int64_t act_workspace_bytes(int M, int K, int r, int B, bool deflate) {
   const ActSplit s = B != 0 ? rotated_split(M, K, r, B, deflate)
-                            : act_split(M, K, 4, deflate ? kMinUnitsDeflated : kMinUnits);
+                            : act_split(M, K, 4, deflate ? kMinUnitsDeflated : plain_min_units(M, r));
   return s.splits > 1 ? split_bytes(s, M, r, deflate ? sizeof(double) : sizeof(float)) : 0;
 }
 
@@ -397,7 +401,7 @@ hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x
                                const uint16_t* L1f, uint8_t* xq, float* xs, uint16_t* t, void* workspace,
                                hipStream_t stream) {
   const int g32 = group == 32 ? 1 : 0;
-  const ActSplit split = workspace != nullptr ? act_split(M, K, 4, kMinUnits) : ActSplit{0, 0};
+  const ActSplit split = workspace != nullptr ? act_split(M, K, 4, plain_min_units(M, r)) : ActSplit{0, 0};
   float* part = split.splits > 1 ? static_cast<float*>(workspace) : nullptr;
   const int nsplit = part != nullptr ? split.splits : 1;
   const int G = part != nullptr ? split.groups : K / kGroup;     // groups per workgroup

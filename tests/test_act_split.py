@@ -66,6 +66,18 @@ def test_workspace_query_reads_only_its_fields(lib):
                 lib.qwam_quantize_act_workspace(ctypes.byref(_c(**kw)), 33, defl) > 0
 
 
+def test_two_splits_need_a_longer_k(lib):
+    """Plain, r <= 32, above 1360 tokens (two splits): K = 3136 takes 9.5 us unsplit and 10.5 split, K = 4096 11.2 and 10.8."""
+    def need(M, K, r=32, defl=0):
+        return lib.qwam_quantize_act_workspace(ctypes.byref(_c(K, r)), M, defl)
+    for M in (1361, 2029, 2048):
+        for r in (16, 32):
+            assert need(M, 3136, r) == 0 and need(M, 3840, r) == 0
+            assert need(M, 3904, r) > 0 and need(M, 3136, r, 1) > 0
+        assert need(M, 3136, 48) > 0 and need(M, 3136, 64) > 0
+    assert need(1360, 3136) > 0
+
+
 CASES = [
     # M, K, r, group, rotated
     (1, 3072, 16, 64, False),
