@@ -62,12 +62,13 @@ qwam_status qwam_probe_empty(void *stream);
  * query: nothing is enqueued), so that a test or a measurement can say which
  * one it reached.  -1 for sizes the layer does not support.
  */
-#define QWAM_PROBE_GEMM_FEW 0            /* up to 64 tokens                                       */
+#define QWAM_PROBE_GEMM_FEW_DIRECT 0     /* up to 64 tokens, operands straight to registers       */
 #define QWAM_PROBE_GEMM_LARGE 1          /* 128 x 128 tiles                                       */
 #define QWAM_PROBE_GEMM_LARGE_HALVES 2   /* 128 x 128 tiles, K in two halves                      */
 #define QWAM_PROBE_GEMM_32X64_W8 3       /* 32 tokens x 64 channels, K over eight waves           */
 #define QWAM_PROBE_GEMM_32X64_W4 4       /* the same, K over four waves                           */
 #define QWAM_PROBE_GEMM_64X64_W4 5       /* 64 tokens x 64 channels, K over four waves            */
+#define QWAM_PROBE_GEMM_FEW_STAGED 6     /* up to 64 tokens, operands through LDS                 */
 int32_t qwam_probe_gemm_form(int32_t M, int32_t N, int32_t K, int32_t group);
 
 /* Message of the calling thread's last failing probe call ("" if none). */

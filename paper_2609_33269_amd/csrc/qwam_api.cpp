@@ -207,7 +207,7 @@ qwam_status qwam_asp_linear(const qwam_layer* L, int32_t M, const uint8_t* xq, c
 int32_t qwam_probe_gemm_form(int32_t M, int32_t N, int32_t K, int32_t group) {
   const char* fn = "qwam_probe_gemm_form";
   if (check_kn(fn, K, N, group) != QWAM_OK || check_m(fn, M) != QWAM_OK) return -1;
-  if (M <= qwam::kSmallM) return QWAM_PROBE_GEMM_FEW;
+  if (M <= qwam::kSmallM) return qwam::small_staged(K) ? QWAM_PROBE_GEMM_FEW_STAGED : QWAM_PROBE_GEMM_FEW_DIRECT;
   switch (qwam::gemm_form(M, N, K, group)) {
     case qwam::GemmForm::kLarge: return QWAM_PROBE_GEMM_LARGE;
     case qwam::GemmForm::kLargeSplit: return QWAM_PROBE_GEMM_LARGE_HALVES;

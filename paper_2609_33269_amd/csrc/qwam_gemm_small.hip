@@ -12,13 +12,17 @@
 //     branch t . L2 on the bf16 matrix cores, the bias, the store).  The
 //     fused few-token layer uses the same split and the same order, so both
 //     paths give the same y from the same codes, scales and t;
-//   * up to K = kDirectK every operand goes straight from HBM/L2 into the MFMA
-//     register layout (lane l: row / column l % 32, half l / 32 of a group, 16
-//     bytes = 32 codes): one memory round trip;
+//   * with a short K (small_staged) every operand goes straight from HBM/L2
+//     into the MFMA register layout (lane l: row / column l % 32, half l / 32 of
+//     a group, 16 bytes = 32 codes): one memory round trip;
 //   * a longer K (STAGED) comes through LDS instead: each wave copies stages of
-//     four groups (one cache line of every row, eight lanes per line,
+//     four groups (128 bytes of every row, eight lanes per row,
 //     buffer_load ... lds) into two buffers of its own, reads a stage into
-//     registers at once and requests its buffer again, with no barrier.  Loads
+//     registers at once and requests its buffer again, with no barrier.  A
+//     stage is one cache line of each row where K is a multiple of 256 and
+//     the waves' ranges, of ceil(K / 512) groups, start on lines (multiples of
+//     four groups); elsewhere it straddles two, and the last stage of a range
+//     copies four groups although it may multiply fewer.  Loads
 //     straight into the operand layout touch each line in four 32-byte pieces,
 //     one chunk after another, and eight waves' 64 rows of lines do not stay
 //     in the 32 KB L1, so each line came from L2 up to four times: at K = 14336,
@@ -283,12 +287,21 @@ __global__ __launch_bounds__(64 * KW) void asp_gemm_small_kernel(
   }
 }
 
-// Up to this K the operands go straight to registers (a wave has at most two
-// groups there, one round trip); above, through LDS.  Direct / staged, graph
-// replays of four layers: K = 1024, N = 4096, M = 16 4.3 / 4.4 us (group 32
-// 4.6 / 4.8); K = 2048, N = 3072, M = 33 5.7 / 4.8; K = 3072, N = 9216, M = 64
-// 19.0 / 15.9; K = 14336, N = 3072, M = 33 20.3 / 13.0 us.
-constexpr int kDirectK = 1024;
+// Whether the operands come through LDS.  By the groups of a wave's range (one
+// round trip up to two), staged / direct over 16000 random shapes (M = 1 .. 64, N
+// = 16 .. 14336, r = 16, 32 and 64), medians of M <= 32 and M > 32 at group 64
+// (group 32: 0 to 6% less in favour from three groups on):
+//   rows of whole lines (K a multiple of 256): 2 groups 1.02 and 0.98, 3 0.95 and
+//   0.91, 4 0.90 and 0.84, 5 0.93 and 0.86, 6 0.90 and 0.82;
+//   other rows: 2 groups 1.05 and 1.04, 3 1.02 and 1.00, 4 0.98 and 0.95, 5 1.02
+//   and 0.99 (a second stage for one group), 6 0.99 and 0.96, 7 0.96 and 0.92.
+// Graph replays of four layers, direct / staged: K = 1024, N = 4096, M = 16 4.3 /
+// 4.4 us; K = 2048, N = 3072, M = 33 5.7 / 4.8; K = 3072, N = 9216, M = 64 19.0 /
+// 15.9; K = 14336, N = 3072, M = 33 20.3 / 13.0 us.
+bool small_staged(int K) {
+  const int range = (K / kGroup + KW - 1) / KW;
+  return K % 256 == 0 ? range > 2 : range == 4 || range > 5;
+}
 
 static unsigned small_blocks(int M, int N) {
   return static_cast<unsigned>(((M + SB - 1) / SB) * ((N + SB - 1) / SB));
@@ -320,7 +333,7 @@ hipError_t launch_asp_gemm_small(int M, int N, int K, int r, int group, const ui
                                  const uint16_t* t, const uint8_t* wq, const float* ws,
                                  const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                                  hipStream_t stream) {
-  if (K > kDirectK)
+  if (small_staged(K))
     return group == 32 ? launch_small_gs<32, true>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream)
                        : launch_small_gs<64, true>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream);
   return group == 32 ? launch_small_gs<32, false>(M, N, K, r, xq, xs, t, wq, ws, L2t, bias, y, stream)

@@ -81,6 +81,8 @@ hipError_t launch_asp_gemm_small(int M, int N, int K, int r, int group, const ui
                                  const uint16_t* L2t, const uint16_t* bias, uint16_t* y,
                                  hipStream_t stream);
 
+bool small_staged(int K);
+
 // Forms of the GEMM for more than kSmallM tokens: 128 x 128 tiles by four
 // waves, the same by eight with K in two halves, and tiles of 32 or 64 tokens
 // x 64 channels with K split over the workgroup's waves (for a few hundred

@@ -428,7 +428,7 @@ def probe_empty(stream=None) -> None:
     _probe_check("qwam_probe_empty", lib().qwam_probe_empty(_stream_ptr(stream)))
 
 
-GEMM_FORMS = ("few", "128x128", "128x128 halves", "32x64 w8", "32x64 w4", "64x64 w4")   # QWAM_PROBE_GEMM_*
+GEMM_FORMS = ("few direct", "128x128", "128x128 halves", "32x64 w8", "32x64 w4", "64x64 w4", "few staged")   # QWAM_PROBE_GEMM_*
 
 
 def probe_gemm_form(M: int, N: int, K: int, group: int = GROUP) -> str:

@@ -28,7 +28,10 @@ TAKEN = [
     (3258, 3136, 1072, 32, "128x128 halves"),     # 44.4, 38.0
     (4096, 3072, 14336, 64, "128x128"),
     (8192, 14336, 3072, 32, "128x128"),
-    (64, 3072, 9216, 64, "few"),
+    (64, 3072, 9216, 64, "few staged"),           # 19.0, 15.9 (straight to registers, through LDS)
+    (33, 14336, 3072, 32, "few staged"),
+    (33, 1280, 3072, 64, "few staged"),           # rows of whole lines: from three groups a wave on
+    (16, 1024, 4096, 64, "few direct"),
 ]
 
 
@@ -46,6 +49,14 @@ def test_two_halves_need_a_long_k_at_group_64(K):
 @pytest.mark.parametrize("M,K,N,group,form", TAKEN)
 def test_faster_forms_are_taken(M, K, N, group, form):
     assert Q.probe_gemm_form(M, N, K, group) == form
+
+
+@pytest.mark.parametrize("K,form", [(1024, "few direct"), (1088, "few direct"), (1344, "few direct"), (1472, "few direct"),
+                                    (1600, "few staged"), (1984, "few staged"), (2112, "few direct"), (2496, "few direct"),
+                                    (2624, "few staged"), (4160, "few staged"), (1536, "few staged"), (2560, "few staged")])
+def test_few_tokens_go_through_lds_where_that_is_faster(K, form):
+    """Rows that are not whole lines: 2-4% slower through LDS at three groups a wave, 1-2% at five."""
+    assert Q.probe_gemm_form(1, 4096, K, 64) == form and Q.probe_gemm_form(64, 16, K, 32) == form
 
 
 def test_unsupported_sizes():

@@ -32,10 +32,12 @@ def _gpu():
 
 SHAPES = [
     # M, K, N, r, group, bias, form
-    (1, 1088, 16, 16, 64, True, "few"),          # ranges of three groups, the last wave idle
-    (33, 2624, 80, 48, 32, False, "few"),        # 41 groups: ranges of six, stages of four and two; one token of block 2
-    (64, 4160, 112, 64, 64, True, "few"),        # 65 groups: ranges of nine
-    (17, 14336, 48, 32, 32, False, "few"),       # ranges of 28: seven full stages
+    (1, 1088, 16, 16, 64, True, "few direct"),   # ranges of three groups, the last wave idle
+    (50, 2368, 48, 32, 32, True, "few direct"),  # 37 groups: ranges of five, chunks of four and one
+    (31, 1280, 48, 48, 64, False, "few staged"),  # 20 groups: ranges of three, the last of two, whole lines
+    (33, 2624, 80, 48, 32, False, "few staged"),  # 41 groups: ranges of six, stages of four and two; one token of block 2
+    (64, 4160, 112, 64, 64, True, "few staged"),  # 65 groups: ranges of nine
+    (17, 14336, 48, 32, 32, False, "few staged"),  # ranges of 28: seven full stages
     (65, 64, 16, 16, 64, True, "32x64 w4"),      # one span, three waves idle, 16 of 64 columns
     (95, 448, 208, 32, 64, False, "32x64 w4"),   # seven spans (last range one span), 31 of 32 tokens
     (97, 832, 1040, 48, 32, True, "32x64 w4"),   # group 32, one token of the last tile
