@@ -21,9 +21,10 @@ namespace qwam {
 // row, whose 4-byte stores then meet in one L2 (rows of spans dealt out one
 // after another left every such line to all eight XCDs' L2s in pieces: 14336 x
 // 3072 47.9 -> 39.9 us, i.e. 5.1 of the 5.2 TB/s that a large copy reaches;
-// 9216 x 3072, group 32 38.3 -> 28.3 us).
-// The first `inv_blocks` workgroups
-// write 1/lambda instead (a launch of its own took 4.8 us behind the pack).
+// 9216 x 3072, group 32 38.3 -> 28.3 us).  Where the spans are no multiple of
+// four the remaining ones are dealt out in the same way, so that no lane idles.
+// The first `inv_blocks` workgroups write 1/lambda instead (a launch of its own
+// took 4.8 us behind the pack).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void pack_weights_kernel(const float* __restrict__ R,
                                                            const float* __restrict__ smooth,
@@ -37,12 +38,15 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const float* __restri
     return;
   }
   const int G = K / kGroup;
-  const int gtiles = (G + 3) / 4;
-  const int tile = static_cast<int>(blockIdx.x) - inv_blocks;
   const int sub = threadIdx.x & 3;
-  const int g = (tile % gtiles) * 4 + ((threadIdx.x >> 2) & 3);
-  const int n = (tile / gtiles) * 16 + (threadIdx.x >> 4);
-  const bool active = g < G && n < N;
+  // (row, span) number of the four lanes: bands of 16 rows, in a band four spans
+  // at a time (the last ones: G % 4), row by row
+  const int team = (static_cast<int>(blockIdx.x) - inv_blocks) * 64 + (threadIdx.x >> 2);
+  const int band = team / (16 * G), v16 = team % (16 * G);
+  const int w = min(4, G - 4 * (v16 >> 6));
+  const int n = 16 * band + (v16 & 63) / w;
+  const int g = 4 * (v16 >> 6) + (v16 & 63) % w;
+  const bool active = n < N;
 
   float v[16];
 #pragma unroll
@@ -357,7 +361,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_deflated_
 // ---------------------------------------------------------------------------
 hipError_t launch_pack_weights(int K, int N, int group, const float* R, const float* smooth, uint8_t* wq,
                                float* ws, uint32_t* wsp, float* inv_smooth, hipStream_t stream) {
-  const int64_t blocks = static_cast<int64_t>((N + 15) / 16) * ((K / kGroup + 3) / 4);
+  const int64_t blocks = (static_cast<int64_t>(N) * (K / kGroup) + 63) / 64;
   const int inv_blocks = (K + 255) / 256;
   hipLaunchKernelGGL(pack_weights_kernel, dim3(static_cast<unsigned>(blocks + inv_blocks)), dim3(256), 0, stream, R,
                      smooth, wq, ws, wsp, inv_smooth, N, K, group == 32 ? 1 : 0, inv_blocks);

@@ -207,3 +207,20 @@ def test_repeat_runs_bit_identical():
         for k in o:
             for a, b in zip(o[k], outs[0][k]):
                 assert (a == b).all(), k
+
+
+@pytest.mark.parametrize("group", [64, 32])
+@pytest.mark.parametrize("N,K", [(272, 64), (80, 128), (1040, 192), (48, 320), (400, 448), (16, 704)])
+def test_weight_pack_remaining_spans(N, K, group):
+    """Spans that are no multiple of four: the pack's workgroups take parts of several bands of 16 rows."""
+    rng = np.random.default_rng(N + K)
+    R = rng.standard_normal((N, K)).astype(np.float32)
+    R[N // 2, :64] = 0.0                                       # a group of scale 0
+    lam = np.exp(rng.standard_normal(K)).astype(np.float32)
+    wq, sw, inv_lam, _ = O.pack_weights(R, lam, group)
+    q, ws, wsp, inv = Q.pack_weights(torch.from_numpy(R).cuda(), torch.from_numpy(lam).cuda(), group=group)
+    assert (q.cpu().numpy() == wq).all() and (ws.cpu().numpy() == sw.T).all() and (inv.cpu().numpy() == inv_lam).all()
+    hi = ws.bfloat16()
+    lo = (ws - hi.float()).bfloat16()
+    want = (hi.view(torch.int16).int() & 0xFFFF) | (lo.view(torch.int16).int() << 16)
+    assert torch.equal(wsp, want)
