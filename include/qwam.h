@@ -210,7 +210,8 @@ qwam_status qwam_quantize_act_deflated(const qwam_layer *L, int32_t M, const uin
  * large K, one workgroup per 16 tokens leaves most of the chip idle; given a
  * workspace, the call splits K over workgroups as well and adds the splits'
  * partial sums of t in a fixed order (t then differs from the unsplit call's
- * in float32 summation order only; deflated, in float64, so its bits agree).
+ * in float32 summation order only; deflated, in float64, so its one rounding
+ * to bf16 gives the same bits except within ~1e-13 relative of a boundary).
  *   deflated   0: as qwam_quantize_act; otherwise as qwam_quantize_act_deflated
  *   workspace  device memory of at least qwam_quantize_act_workspace(L, M,
  *              deflated) bytes, 16-byte aligned, owned by the caller; its
@@ -223,7 +224,7 @@ qwam_status qwam_quantize_act_ws(const qwam_layer *L, int32_t M, int32_t deflate
 
 /* Bytes of workspace with which qwam_quantize_act_ws splits K for (L, M):
  * 0 where it does not, -1 for an unsupported layer or M.  Reads K, r, group
- * and hadamard of L only. */
+ * and hadamard of L only (N need not be set). */
 int64_t qwam_quantize_act_workspace(const qwam_layer *L, int32_t M, int32_t deflated);
 
 /*

@@ -337,9 +337,9 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
 //   * A pivot below 1e-13 of the largest diagonal entry (a block of lower
 //     rank) is raised to that floor, so the inverse stays finite; the next
 //     iterations refill such a direction.
-//   * A wave inverts its diagonal block right after it has factored it, while
-//     the others go on (the whole inverse was a second chain over the blocks,
-//     10 of this kernel's 23 us; the basis update does that substitution).
+//   * After the last block every wave inverts its own diagonal block, all four
+//     at once (the whole inverse was a second chain over the blocks, 10 of this
+//     kernel's 23 us; the basis update does that substitution).
 // Inside a block the row of R reaches the wave's other lanes by cross-lane
 // reads (no LDS round trip on the chain of pivots).
 constexpr int CB = 16;          // rows per block (and per wave)

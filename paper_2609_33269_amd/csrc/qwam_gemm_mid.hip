@@ -41,7 +41,6 @@ struct MidShape {
   static constexpr int GPS = KC * NS;                           // scale groups per stage
   static constexpr int TM = 32 * TB, TN = 32 * WB;
   static constexpr int STAGE = (TM + TN) * (ROWB + GPS * 4);    // codes and scales, per wave
-  static constexpr int NI = (TM + TN) / 8 + GPS * (TM + TN) / 64;   // copies per stage
 };
 
 // 16-byte chunk slot permutation of a 128-byte row: 16 consecutive rows reading
@@ -56,7 +55,7 @@ __global__ __launch_bounds__(64 * MW, 8 / MW) void asp_gemm_mid_kernel(
     const uint8_t* __restrict__ wq, const uint32_t* __restrict__ wsp, const uint16_t* __restrict__ L2t,
     const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, int M, int N, int K) {
   using S = MidShape<GS, TB, WB>;
-  constexpr int NS = S::NS, GPS = S::GPS, TM = S::TM, TN = S::TN, NI = S::NI;
+  constexpr int NS = S::NS, GPS = S::GPS, TM = S::TM, TN = S::TN;
   static_assert(WB == 2 && (TB == 1 || TB == 2), "two weight blocks, one or two token blocks");
   static_assert(TB * WB * 16 * 256 <= S::STAGE, "a wave's partial tile fits in its stage buffer");
   __shared__ __attribute__((aligned(16))) uint8_t st0[MW][S::STAGE];
