@@ -262,15 +262,16 @@ def _quantize(deflated: bool, name: str, layer: PackedLayer, x: torch.Tensor, st
     else:
         xq, xs, t = out
     c = layer.c_struct()
-    # few tokens and a large K: the call splits K over workgroups through a workspace
-    # (a bare stream handle has no pool to take one from: the call runs unsplit)
-    need = lib().qwam_quantize_act_workspace(ctypes.byref(c), M, deflated) if pooled else 0
-    ws = _workspace(need, dev, stream)
-    st = lib().qwam_quantize_act_ws(ctypes.byref(c), M, deflated, _req(x, "x", torch.bfloat16, (M, layer.K)),
-                                    _req(xq, "xq", torch.uint8, (M, layer.K // 2)),
-                                    _req(xs, "xs", torch.float32, (layer.K // layer.group, M)),
-                                    _req(t, "t", torch.bfloat16, (M, layer.r)),
-                                    None if ws is None else ws.data_ptr(), max(need, 0), _stream_ptr(stream))
+    ptrs = (_req(x, "x", torch.bfloat16, (M, layer.K)), _req(xq, "xq", torch.uint8, (M, layer.K // 2)),
+            _req(xs, "xs", torch.float32, (layer.K // layer.group, M)), _req(t, "t", torch.bfloat16, (M, layer.r)))
+    if pooled:
+        # few tokens and a large K: the call splits K over workgroups through a workspace
+        need = lib().qwam_quantize_act_workspace(ctypes.byref(c), M, deflated)
+        ws = _workspace(need, dev, stream)
+        st = lib().qwam_quantize_act_ws(ctypes.byref(c), M, deflated, *ptrs, None if ws is None else ws.data_ptr(),
+                                        max(need, 0), _stream_ptr(stream))
+    else:     # a bare stream handle has no pool to take a workspace from: the call runs unsplit
+        st = getattr(lib(), name)(ctypes.byref(c), M, *ptrs, _stream_ptr(stream))
     _check(name, st)
     return xq, xs, t
 
