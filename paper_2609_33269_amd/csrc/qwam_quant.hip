@@ -107,9 +107,11 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const float* __restri
 // and its sums of t go to a workspace that split_t_kernel adds up: one
 // workgroup's reads of x and L1 (32 + 2 r bytes per channel) are what a call
 // of a few tokens waits for, at about 50 B/ns per CU
-// (33 tokens, K = 14336: 26.3 us in three workgroups, 7.7 us in 168).
+// (33 tokens, K = 14336: 26.3 us in three workgroups, 7.7 us in 168).  SPLIT
+// kernels are instances of their own: the part's bounds and the choice of where
+// the sums go cost a call with the whole K 0.1 us (1-4% up to K = 2752).
 // ---------------------------------------------------------------------------
-template <int RANK, bool INV_LDS>
+template <int RANK, bool INV_LDS, bool SPLIT>
 __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
     const uint16_t* __restrict__ x, const float* __restrict__ inv_smooth,
     const uint16_t* __restrict__ L1f, uint8_t* __restrict__ xq, float* __restrict__ xs,
@@ -128,9 +130,10 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
   const int rows = min(16, M - m0);
   const int G = K / kGroup;
   // the workgroup's groups (all of K, or split blockIdx.y), then the wave's
-  const int wg_begin = static_cast<int>(blockIdx.y) * groups_per_wg;
+  const int wg_begin = SPLIT ? static_cast<int>(blockIdx.y) * groups_per_wg : 0;
+  const int wg_end = SPLIT ? min(G, wg_begin + groups_per_wg) : G;
   const int g_begin = wg_begin + wave * groups_per_wave;
-  const int g_end = min(min(G, wg_begin + groups_per_wg), g_begin + groups_per_wave);
+  const int g_end = min(wg_end, g_begin + groups_per_wave);
 
   // the workgroup's 16 rows of x, xq; out-of-range rows read as zero / are dropped
   const buf_rsrc x_rsrc = make_rsrc(x + static_cast<int64_t>(m0) * K, static_cast<uint32_t>(rows) * K * 2u);
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_kernel(
 
   store_t_partials<RB>(red, wave, lane, acc);
   __syncthreads();
-  if (part != nullptr) store_split_t<RANK>(red, nwaves, m0, part);
+  if constexpr (SPLIT) store_split_t<RANK>(red, nwaves, m0, part);
   else reduce_t<RANK>(red, nwaves, rows, t + static_cast<int64_t>(m0) * RANK, static_cast<float*>(nullptr));
 }
 
@@ -267,9 +270,10 @@ __global__ __launch_bounds__(64 * act_waves<RANK>()) void quantize_act_deflated_
   const int m0 = blockIdx.x * 16;
   const int rows = min(16, M - m0);
   const int G = K / kGroup;
-  const int wg_begin = static_cast<int>(blockIdx.y) * groups_per_wg;
+  const int wg_begin = PHASE == Phase::kAll ? 0 : static_cast<int>(blockIdx.y) * groups_per_wg;
+  const int wg_end = PHASE == Phase::kAll ? G : min(G, wg_begin + groups_per_wg);
   const int g_begin = wg_begin + wave * groups_per_wave;
-  const int g_end = min(min(G, wg_begin + groups_per_wg), g_begin + groups_per_wave);
+  const int g_end = min(wg_end, g_begin + groups_per_wave);
 
   const buf_rsrc x_rsrc = make_rsrc(x + static_cast<int64_t>(m0) * K, static_cast<uint32_t>(rows) * K * 2u);
   const buf_rsrc q_rsrc = make_rsrc(xq + static_cast<int64_t>(m0) * (K / 2), static_cast<uint32_t>(rows) * (K / 2));
@@ -411,7 +415,7 @@ hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x
   const int G = part != nullptr ? split.groups : K / kGroup;     // groups per workgroup
   // 1/lambda is staged in LDS when the slice fits (16384 channels); a longer one is read from global memory
   const bool inv_lds = G * kGroup <= 16384;
-  auto go = [&](auto kernel_lds, auto kernel_global, int max_waves) {
+  auto go = [&](auto kernel, int max_waves) {
     int nwaves = G < max_waves ? G : max_waves;
     int gpw = (G + nwaves - 1) / nwaves;
     if (G >= 64) {   // wave ranges of whole 4-group line chunks (below, the waves keep one group or more each)
@@ -422,22 +426,29 @@ hipError_t launch_quantize_act(int M, int K, int r, int group, const uint16_t* x
     const size_t lds = static_cast<size_t>(nwaves) * (16 * r + (inv_lds ? gpw * kGroup : 0)) * sizeof(float) +
                        (gpw % 4 == 0 ? static_cast<size_t>(nwaves) * 2048 : 0);
     if (lds > 64 * 1024) {   // opt in to more than 64 KB of dynamic LDS
-      const void* fn = inv_lds ? reinterpret_cast<const void*>(kernel_lds) : reinterpret_cast<const void*>(kernel_global);
-      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((inv_lds ? kernel_lds : kernel_global), dim3((M + 15) / 16, nsplit), dim3(64 * nwaves), lds, stream,
+    hipLaunchKernelGGL(kernel, dim3((M + 15) / 16, nsplit), dim3(64 * nwaves), lds, stream,
                        x, inv_smooth, L1f, xq, xs, t, part, M, K, G, gpw, g32);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess || part == nullptr ? e : launch_split_t(M, r, nsplit, part, t, stream);
   };
+#define QWAM_ACT_CASE(R)                                                                  \
+  case R:                                                                                 \
+    /* a split's slice of 1/lambda always fits in LDS */                                  \
+    if (part != nullptr) return go(quantize_act_kernel<R, true, true>, act_waves<R>());   \
+    return inv_lds ? go(quantize_act_kernel<R, true, false>, act_waves<R>())              \
+                   : go(quantize_act_kernel<R, false, false>, act_waves<R>());
   switch (r) {
-    case 16: return go(quantize_act_kernel<16, true>, quantize_act_kernel<16, false>, act_waves<16>());
-    case 32: return go(quantize_act_kernel<32, true>, quantize_act_kernel<32, false>, act_waves<32>());
-    case 48: return go(quantize_act_kernel<48, true>, quantize_act_kernel<48, false>, act_waves<48>());
-    case 64: return go(quantize_act_kernel<64, true>, quantize_act_kernel<64, false>, act_waves<64>());
+    QWAM_ACT_CASE(16)
+    QWAM_ACT_CASE(32)
+    QWAM_ACT_CASE(48)
+    QWAM_ACT_CASE(64)
     default: return hipErrorInvalidValue;
   }
+#undef QWAM_ACT_CASE
 }
 
 hipError_t launch_quantize_act_deflated(int M, int K, int r, int group, const uint16_t* x,
