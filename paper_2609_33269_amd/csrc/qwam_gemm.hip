@@ -700,7 +700,7 @@ static hipError_t launch_asp_gemm_gs(int M, int N, int K, int r, const uint8_t* 
 //
 // Against 23000 random shapes (M = 65 .. 8192, K = 64 .. 14336, N = 16 .. 14336,
 // every rank) the estimates are wrong at the edges of the fit, where the lines
-// below hold them back: with them 0.7% of the choices of another form are more
+// below hold them back: with them 0.5% of the choices of another form are more
 // than 3% slower than the large tiles (without: 5.5%, up to 46%), and the choice
 // is 0.8% slower than the best form on average (1.2%).  The large tiles keep a
 // call
@@ -716,6 +716,10 @@ static hipError_t launch_asp_gemm_gs(int M, int N, int K, int r, const uint8_t* 
 //     their second round 7.0 / 8.5 us, 64 x 64 tiles two to a CU 7.0 / 7.7 us,
 //     beyond 9.9 / 15.3 us), and at group 32 up to 512 channels when the large
 //     tiles are more than CUs too (14.2 / 18.8 us);
+//   * within 17%, against small tiles whose waves' ranges (whole stages) add up to
+//     more than 1.3 K, above 128 large tiles and K = 1024: the estimate goes
+//     by K (K = 2112, four waves: three ranges of three stages and an idle wave;
+//     M = 2207, N = 1008 17.7 / 19.6 us);
 //   * against K in two halves, at group 64 below K = 2816 (4-9% slower there;
 //     from 3072 on 2-10% faster, at group 32 from 1024 on 2-23%).  The
 //     halves are whole stages, so an odd number of stages costs one more.
@@ -751,10 +755,18 @@ GemmForm gemm_form(int M, int N, int K, int group) {
   const bool usable[5] = {true, K >= (g32 ? 1024 : 2816), !short_k && (!one_stage || t32 <= 256),
                           !short_k && (!one_stage || t32 <= 512), !short_k && (!one_stage || t64 <= 256)};
   const int64_t keep_halves = ns[0] - ns[0] / (large > 256 ? 12 : 32);
-  const int64_t keep_small = !g32 && M > 3000 && large > 128 ? ns[0] - ns[0] / 5 : keep_halves;
+  const bool tall = !g32 && M > 3000 && large > 128;
+  const auto keep_small = [&](int waves) {
+    const int stages = (K + 4 * kGroup - 1) / (4 * kGroup);
+    const int ranges_k = 4 * kGroup * waves * ((stages + waves - 1) / waves);
+    const bool uneven = K > 1024 && large > 128 && 10 * ranges_k > 13 * K;
+    return tall ? ns[0] - ns[0] / 5 : uneven ? ns[0] - ns[0] / 6 : keep_halves;
+  };
   int best = 0;
-  for (int i = 1; i < 5; ++i)
-    if (usable[i] && ns[i] < (i == 1 ? keep_halves : keep_small) && (best == 0 || ns[i] < ns[best])) best = i;
+  for (int i = 1; i < 5; ++i) {
+    const int64_t keep = i == 1 ? keep_halves : keep_small(i == 2 ? 8 : 4);
+    if (usable[i] && ns[i] < keep && (best == 0 || ns[i] < ns[best])) best = i;
+  }
   return static_cast<GemmForm>(best);
 }
 

@@ -17,6 +17,8 @@ KEPT = [
     (4352, 128, 288, 64),     # 5.2, 5.4: one stage
     (7976, 3136, 352, 64),    # 23.3, 28.9: many tokens, few channels
     (4501, 3648, 1072, 64),   # 39.3, 45.4
+    (2207, 2112, 1008, 64),   # 17.7, 19.6: the waves' ranges are whole stages (three of three, none for the fourth)
+    (265, 2112, 8416, 64),    # 16.5, 18.2
 ]
 TAKEN = [
     (415, 14336, 3072, 64, "64x64 w4"),           # 75.7, 35.7
